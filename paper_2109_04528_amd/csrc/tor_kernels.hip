@@ -386,30 +386,76 @@ __device__ __forceinline__ void elim_lds(S *node, int nb, int s, int lane, RT<S>
     __syncthreads();
 }
 
-__device__ __forceinline__ void st_g(double *p, double v) { *(__attribute__((address_space(1))) double *)p = v; }
-template <class S>
-__device__ __forceinline__ void st_g(S *p, S v)
+// 16-byte granule gi of a node, from LDS or (GLOBAL) global memory
+template <bool GLOBAL, class S>
+__device__ __forceinline__ dv2 ld_gran(const S *node, int gi)
 {
-    dv2 raw;
-    __builtin_memcpy(&raw, &v, 16);
-    *(__attribute__((address_space(1))) dv2 *)p = raw;
+    const S *p = node + EPG((int)sizeof(S)) * gi;
+    if constexpr (GLOBAL)
+        return *(const __attribute__((address_space(1))) dv2 *)p;
+    return *reinterpret_cast<const dv2 *>(p);
+}
+template <bool GLOBAL, class S>
+__device__ __forceinline__ void st_gran(S *node, int gi, dv2 v)
+{
+    S *p = node + EPG((int)sizeof(S)) * gi;
+    if constexpr (GLOBAL)
+        *(__attribute__((address_space(1))) dv2 *)p = v;
+    else
+        *reinterpret_cast<dv2 *>(p) = v;
 }
 
 // the first s modes of a node with snb blocks per granule array, copied into
-// a node with dnb (global source or destination as flagged)
+// a node with dnb (global source or destination as flagged), in 16-byte
+// granules.  What bounds it is the latency of its loads (a root starts with
+// one such copy of its matrix): each lane issues 8 loads (4 on the 16-byte
+// paths, whose registers allow no more) before it stores any.
 template <class S, bool SRC_G, bool DST_G>
 __device__ __forceinline__ void copy_node(const S *src, int snb, S *dst, int dnb, int s, int lane)
 {
-    constexpr int G = EPG((int)sizeof(S));
-    const int ga = G * NB(s);  // scalars of one granule array
-    for (int e = lane; e < NSZ(s); e += 64) {
-        const int g = e / ga, r = e - g * ga;
-        const S v = SRC_G ? ld_g(&src[g * G * snb + r]) : src[g * G * snb + r];
-        if constexpr (DST_G)
-            st_g(&dst[g * G * dnb + r], v);
-        else
-            dst[g * G * dnb + r] = v;
+    constexpr int GPB = 4 / EPG((int)sizeof(S));  // granule arrays
+    constexpr int U = GPB == 2 ? 4 : 1;
+    const int nb = NB(s);
+    for (int b0 = lane; b0 < nb; b0 += 64 * U) {
+        dv2 v[U][GPB];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (b0 + 64 * u < nb)
+#pragma unroll
+                for (int g = 0; g < GPB; ++g)
+                    v[u][g] = ld_gran<SRC_G>(src, g * snb + b0 + 64 * u);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (b0 + 64 * u < nb)
+#pragma unroll
+                for (int g = 0; g < GPB; ++g)
+                    st_gran<DST_G>(dst, g * dnb + b0 + 64 * u, v[u][g]);
     }
+}
+
+// the first SM modes of a node in LDS, moved to the front of its buffer with
+// the stride NB(SM) (the source's granule arrays start at node and are nb
+// blocks apart, nb >= NB(SM)): the two overlap, so every granule is read
+// before any is written
+template <class S, int SM>
+__device__ __forceinline__ void restride_node(S *node, int nb, int s, int lane)
+{
+    constexpr int GPB = 4 / EPG((int)sizeof(S)), IT = (NB(SM) + 63) / 64;
+    const int n = NB(s);
+    dv2 v[IT][GPB];
+#pragma unroll
+    for (int i = 0; i < IT; ++i)
+        if (lane + 64 * i < n)
+#pragma unroll
+            for (int g = 0; g < GPB; ++g)
+                v[i][g] = ld_gran<false>(node, g * nb + lane + 64 * i);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IT; ++i)
+        if (lane + 64 * i < n)
+#pragma unroll
+            for (int g = 0; g < GPB; ++g)
+                st_gran<false>(node, g * NB(SM) + lane + 64 * i, v[i][g]);
 }
 
 // ---------------------------------------------------------------------------
@@ -806,23 +852,31 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
     const TierB<S> tb{bufB, srcOff, srcNB, srcDet, nodeRec, blkRec, nInv, nBa, ndet};
     S *wscr = reinterpret_cast<S *>(prm.scratch + (long long)blockIdx.x * prm.scratch_stride);
 
-    for (;;) {
-        // every lane issues the same atomic (only lane 0 adds 1), so the
-        // ticket needs no lane-dependent control flow; lane 0's old value is
-        // the ticket, taken into scalar registers
-        const unsigned long long item = bcast_first(atomicAdd(prm.counter, lane == 0 ? 1ull : 0ull));
-        if ((long long)item >= prm.total_items)
-            break;
+    // The first item of each wave is its own block's; the queue counter hands
+    // out the ones after the grid's.  A launch of no more items than waves
+    // touches no counter at all (its one address serves the whole device's
+    // waves one by one: 1024 of them took 13 to 17 us to get their first
+    // tickets).  Every lane adds 1 with nothing lane-dependent in the source,
+    // which the compiler turns into one atomic of 64 (adding 1 from lane 0
+    // only became a 64-step loop over the lanes, 2 us), so a ticket is a 64th
+    // of the old value.
+    const auto *probs = (const __attribute__((address_space(4))) ProblemDesc *)prm.probs;
+    long long item = blockIdx.x;
+    for (; item < prm.total_items;
+         item = (long long)gridDim.x < prm.total_items
+                    ? (long long)gridDim.x + (long long)(bcast_first(atomicAdd(prm.counter, 1ull)) >> 6)
+                    : prm.total_items) {
         int lo = 0, hi = prm.nprob - 1;  // last problem with item_begin <= item
         while (lo < hi) {
             int mid = (lo + hi + 1) >> 1;
-            if (prm.probs[mid].item_begin <= (long long)item)
+            if (probs[mid].item_begin <= item)
                 lo = mid;
             else
                 hi = mid - 1;
         }
-        const ProblemDesc P = prm.probs[lo];
-        const long long root = P.root_begin + ((long long)item - P.item_begin);
+        const ProblemDesc P = {probs[lo].C,          probs[lo].slots,      probs[lo].N,     probs[lo].k,
+                               probs[lo].root_begin, probs[lo].item_begin, probs[lo].nroots};
+        const long long root = P.root_begin + (item - P.item_begin);
         const int N = P.N, k = P.k, LA = N - R, D = LA - k;
         const S *C = reinterpret_cast<const S *>(P.C);
         // the wave's stack (tslot_off): the root node, tier-A slots k+1 ..
@@ -842,6 +896,7 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
         int rnb = NB(N);
         RT<S> rdet = rconst<RT<S>>(1.0);
         int rinc = 0;
+        bool in_lds = false;  // the first leaf's node is in place in LDS
         const unsigned long long rbits = (unsigned long long)root & ((1ull << k) - 1);
         const int l0 = rbits ? __builtin_ctzll(rbits) : k;  // first included level
         if (rbits && NSZ(N - l0) <= kBufScalars) {
@@ -856,10 +911,14 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
                     ++rinc;
                 }
             }
-            copy_node<S, false, true>(bufB, nb0, wscr, NB(N - k), N - k, lane);
-            __syncthreads();
+            // later leaves read the root node from the stack (a root of one
+            // leaf has none); the first one is already here
+            if (D > 0)
+                copy_node<S, false, true>(bufB, nb0, wscr, NB(N - k), N - k, lane);
+            restride_node<S, R + X0>(bufB, nb0, min(R + X0, N - k), lane);
             rsrc = wscr;
             rnb = NB(N - k);
+            in_lds = true;
         } else {
             for (int l = 0; l < k; ++l) {
                 if ((rbits >> l) & 1) {
@@ -887,18 +946,10 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
             RT<S> ldet;
             int linc;
             if (x == 0) {
-                if constexpr (X0) {
-                    // the first R+1 modes of the root node (R when the root
-                    // is the leaf), restrided to NB(R + 1)
-                    copy_node<S, true, false>(rsrc, rnb, bufB, NB(R + 1), min(R + 1, N - k), lane);
-                } else {
-                    // the first R modes of the root node, restrided to NB(R)
-                    constexpr int GA = EPG((int)sizeof(S)) * NB(R);  // scalars per granule array
-                    for (int e = lane; e < NSZ(R); e += 64) {
-                        const int g = e / GA;
-                        bufB[e] = ld_g(&rsrc[g * EPG((int)sizeof(S)) * rnb + (e - g * GA)]);
-                    }
-                }
+                // the first R modes of the root node (real path R + 1, or R
+                // when the root is the leaf), restrided
+                if (!in_lds)
+                    copy_node<S, true, false>(rsrc, rnb, bufB, NB(R + X0), min(R + X0, N - k), lane);
                 ldet = rdet;
                 linc = rinc;
             } else {
@@ -972,7 +1023,7 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
         if (lane == 0) {
             // slots are overwritten, never accumulated, so running a root
             // again (the host's recovery from a numeric failure) is idempotent
-            const bool forced = (long long)item + 1 == prm.fail_item1;
+            const bool forced = item + 1 == prm.fail_item1;
             double *sl = P.slots + 4 * root;
             sl[0] = forced ? __builtin_nan("") : h;
             sl[1] = l;
