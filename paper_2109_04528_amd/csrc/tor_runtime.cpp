@@ -185,8 +185,8 @@ int launch_grid(const tor_ctx *ctx, int path, int Nmax)
     return default_grid(ctx, path);
 }
 
-// split depth: the tuned value for this size, else about four subtree roots
-// per persistent wave, never deeper than the levels above the last R modes
+// split depth: the tuned value for this size, else by the rules below, never
+// deeper than the levels above the last R modes
 int choose_k(const tor_ctx *ctx, int N, int path)
 {
     const int LA = N - path_R(path);
@@ -197,40 +197,34 @@ int choose_k(const tor_ctx *ctx, int N, int path)
     const TuneEntry &t = ctx->tune[path][std::min(N, MAX_N)];
     if (t.valid)
         return std::min(t.k, LA);
-    int g = 1;
+    int g = 1;  // the grid has more than 2^(g-1) and at most 2^g waves
     while ((1 << g) < default_grid(ctx, path))
         ++g;
-    // Every root first recomputes its k eliminations in global memory, which a
-    // short root does not amortise, so no more roots than leave each about
-    // 64 tier-A leaves on the real path (k <= LA - 6) and 32 on the 16-byte
-    // paths (k <= LA - 5), within [g, g + 2] on the real path (one to four
-    // roots per wave of the 2^g grid) and [g - 1, g + 3] on the 16-byte
-    // paths, whose leaves are a quarter the size and whose launches end more
-    // evenly with more roots.  The autotuner's picks this follows:
-    // real n = 26 k = 11 (0.26 ms against 0.34 at k = 13), n = 30 k = 13;
-    // complex n = 24 k = 10 (0.26 against 0.33 at 13), n = 30 k = 14 (10.1
-    // against 10.9 at 13); double-double n = 30 k = 14 (24.1 against 24.9).
-    const int lo = path == PATH_REAL ? g : g - 1;
-    const int hi = path == PATH_REAL ? g + 2 : g + 3;
-    // real path, LA from g - 1 to g + 2 (n = 21..24 on the 2048-wave grid):
-    // the grid cannot be filled with roots of many leaves, and one leaf per
-    // root leaves each wave's root set-up unshared; roots of two to eight
-    // leaves at g - 1 measured fastest (n = 22: 0.052 ms against 0.079 at
-    // k = g = LA, n = 23: 0.069 against 0.078)
-    if (path == PATH_REAL && LA >= g - 1 && LA <= g + 2)
-        return std::min(LA - 1, g - 1);
-    // the 16-byte paths' leaves are a quarter the size: 32 leaves per root
-    // (n = 26: complex 0.73 ms against 0.83 with 64, double-double 1.85
-    // against 2.07; n = 27 double-double 3.23 against 3.64)
-    const int leaves = path == PATH_REAL ? 6 : 5;
-    const int k = std::min(LA, std::max(lo, std::min(hi, LA - leaves)));
-    // real path: two roots per wave end the launch worst (the two waves of a
-    // SIMD run at different speeds, and the faster ones run dry with half
-    // their share left to the others): n = 29 1.61 ms at k = g + 1 against
-    // 1.37 at g + 2, n = 28 0.84 against 0.73
-    if (path == PATH_REAL && k == g + 1)
-        return std::min(LA, g + 2);
-    return k;
+    // One root per wave while the leaves allow it (the first root costs a wave
+    // no ticket), so that a launch ends with every wave at about the same
+    // place.  From there on the time goes to whichever is the smaller loss:
+    // the waves that share a SIMD run at different speeds, which several
+    // roots per wave even out, and every root pays its own set-up (up to k
+    // eliminations).  Kernel times on a 256-CU part, us:
+    if (path == PATH_REAL && default_grid(ctx, path) == 1 << g) {
+        // 2048 waves: n = 22 (LA = 11) 29.1 at k = 11, 29.8 at 10, 40.6 at 9;
+        // n = 24 67.1 at 11, 77.0 at 10, 82.4 at 12, 117 at 13; n = 27 366 at
+        // 11, 376 at 13, 418 at 12; n = 28 692 at 13, 726 at 11, 812 at 12;
+        // n = 30 2558 at 13, 2631 at 14, 2800 at 11, 3207 at 12 (two roots per
+        // wave end worst: a wave's second root starts when the others' do)
+        return std::min(LA, LA <= g + 5 ? g : g + 2);
+    }
+    // 1792 waves on the 16-byte paths (and a grid cut to less than a power of
+    // two of waves): at k = g a few waves run a second root alone, so k = g - 1.
+    // complex n = 23 (LA = 14) 116 at k = 10, 126 at 11, 125 at 12; n = 24 202
+    // at 12, 213 at 10, 221 at 11; n = 25 357 at 12, 413 at 10 and 11; n = 27
+    // 1310 at 14, 1318 at 12, 1334 at 13.  Double-double, whose leaves take
+    // longest: n = 25 (LA = 16) 896 at 10, 925 at 13, 1026 at 11; n = 26 1699 at
+    // 14, 1747 at 10, 1763 at 13
+    const int one = g - 1;
+    if (path == PATH_QUAD)
+        return std::min(LA, LA <= g + 5 ? one : g + 3);
+    return std::min(LA, LA <= g + 3 ? one : LA <= g + 6 ? g + 1 : g + 3);
 }
 
 int ensure_ws(tor_ctx *ctx, size_t bytes)
