@@ -54,9 +54,12 @@ struct ProblemDesc {
     long long nroots;      // roots handled by this launch
 };
 
+struct StageInfo;
+
 struct MainParams {
-    const ProblemDesc *probs;
+    const ProblemDesc *probs;     // nprob descriptors; null: `one` is the only matrix
     int nprob;
+    int gate_path;                // with gate
     long long total_items;
     unsigned long long *counter;  // queue head, zero before the launch
     char *scratch;                // per-wave stack of the upper include levels
@@ -66,6 +69,11 @@ struct MainParams {
     double *terms;                // every-term launch (one matrix, all roots): the
                                   // signed term of each subset, indexed by subset
                                   // (bit N-1-l = decision at level l); else null
+    const StageInfo *gate;        // run only if the staging kernel gave gate_path (null: always)
+    double *result;               // a launch of one root: its slot's values go here too (or null)
+    long long *clock;             // the device clock at the kernel's start goes here (or null)
+    double ms_per_tick;           // of that clock
+    ProblemDesc one;
 };
 // root slot flag (fourth double): a tested pivot failed (I - O is not
 // positive definite), or the root's sum is not finite (a numeric failure,
@@ -108,7 +116,7 @@ constexpr int STAGE_BAD_INPUT = 1;  // a value is not finite, or a required test
 
 struct StageInfo {
     int status;   // 0, or STAGE_BAD_INPUT
-    int path;     // PATH_* of the staged form
+    int path;     // PATH_* of the staged form (-1 with a bad status)
     int N;        // its modes (after padding)
     int unused;
     double cmax;  // max |I - O|
@@ -116,7 +124,7 @@ struct StageInfo {
 
 struct StageDesc {
     const double *O;   // complex128 row-major (re, im), leading dimension ld
-    long ld;           // in complex elements
+    long ld;           // in complex elements; 0: the lower triangle alone, packed by rows (pidx)
     const int *sel;    // null, or the n modes (increasing) of an M-mode O
     int n, M;
     unsigned flags;    // STAGE_*
@@ -124,6 +132,9 @@ struct StageDesc {
     void *out;         // the staged form (bytes: staged_bytes)
     StageInfo *info;
 };
+
+// inputs up to this many modes are staged through LDS, each value read once
+constexpr int STAGE_LDS_MODES = 40;
 
 // sum_{i=1..s} 2i(i+1): scalars of all node sizes 1..s
 __host__ __device__ constexpr long long Gsum(long long s) { return s <= 0 ? 0 : 2 * s * (s + 1) * (s + 2) / 3; }
@@ -198,6 +209,34 @@ hipError_t launch_math_probe(const double *x, double *out, int count, hipStream_
 // FP64 FMA throughput probe: blocks x 256 lanes, iters x 16 FMAs each
 hipError_t launch_fma_peak(double *out, int blocks, int iters, hipStream_t s);
 constexpr int FMA_PROBE_CHAINS = 16;
+// One evaluation in one go: the staging kernel, the recursive kernel of each
+// path the matrix may turn out to have (the ones the staging kernel does not
+// choose return at once) and the reduction, with nothing for the host to do in
+// between and everything small passed as kernel arguments.  stage false: the
+// matrix is staged already (st.info holds the verdict).
+struct EvalOne {
+    bool stage;
+    StageDesc st;                  // st.info: device memory
+    StageInfo *host_info;          // pinned: a copy of the verdict
+    unsigned long long *counters;  // device: a queue head per run
+    int nrun;
+    struct Run {
+        int path;
+        ProblemDesc P;
+        char *scratch;
+        long long stride;
+        int grid;
+    } run[2];
+    bool dd;           // sum in double-double
+    long long *clock;  // device: when the recursive kernel started
+    double *result;    // pinned: hi, lo, sum of |t|, flag, and the recursive kernel's time in ms
+};
+// null in a host-only build of the runtime without the kernels, which then
+// takes the general path
+__attribute__((weak)) hipError_t launch_eval_one(const EvalOne &e, hipStream_t s);
+// its staging kernel (tor_stage.hip)
+hipError_t launch_stage_one(const StageDesc &d, StageInfo *host_info, unsigned long long *zero, int nzero, hipStream_t s);
+
 // defined in tor_stage.hip
 hipError_t launch_stage(const StageDesc *descs, int count, hipStream_t s);
 hipError_t launch_sqrt_det(const double *O, long ld, int M, c64 *scratch, double *out, hipStream_t s);

@@ -846,7 +846,11 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
     __shared__ uint32_t blkRec[NB(R - 1)];
     __shared__ unsigned long long nodeRec[(1 << BL) - 1];
 
+    if (prm.gate && prm.gate->path != prm.gate_path)
+        return;  // the matrix has another path, or is not valid
     const int lane = threadIdx.x;
+    if (prm.clock && blockIdx.x == 0 && lane == 0)
+        *prm.clock = wall_clock64();
     build_tables<S, R, BL + 1, L>(srcOff, srcNB, srcDet, nodeRec, blkRec, lane);
     __syncthreads();
     const TierB<S> tb{bufB, srcOff, srcNB, srcDet, nodeRec, blkRec, nInv, nBa, ndet};
@@ -860,7 +864,12 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
     // which the compiler turns into one atomic of 64 (adding 1 from lane 0
     // only became a 64-step loop over the lanes, 2 us), so a ticket is a 64th
     // of the old value.
-    const auto *probs = (const __attribute__((address_space(4))) ProblemDesc *)prm.probs;
+    // the descriptors are read where they lie, by scalar loads: prm.one in the
+    // kernel's arguments (prm is the first of them) unless there is a list
+    typedef const __attribute__((address_space(4))) ProblemDesc CDesc;
+    CDesc *probs = prm.probs ? (CDesc *)prm.probs
+                             : (CDesc *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
+                                         offsetof(MainParams, one));
     long long item = blockIdx.x;
     for (; item < prm.total_items;
          item = (long long)gridDim.x < prm.total_items
@@ -1029,6 +1038,11 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
             sl[1] = l;
             sl[2] = ab;
             sl[3] = anybad ? SLOT_NOT_PD : (forced || !__builtin_isfinite(h)) ? SLOT_NUMERIC : 0.0;
+            if (prm.result) {  // the matrix's only root: the reduction would give the same
+                for (int j = 0; j < 4; ++j)
+                    prm.result[j] = sl[j];
+                prm.result[4] = (double)(wall_clock64() - *prm.clock) * prm.ms_per_tick;
+            }
         }
     }
 }
@@ -1052,12 +1066,11 @@ __device__ inline void red_step(double &h, double &l, double &ab, double &bad, i
 }
 
 template <bool DD>
-__global__ void __launch_bounds__(RED_THREADS) tor_reduce(const ProblemDesc *probs, double *results)
+__device__ __forceinline__ void reduce_matrix(const ProblemDesc &P, double *result)
 {
     constexpr int NW = RED_THREADS / 64;
     __shared__ double part[4][NW];
-    const int q = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const ProblemDesc P = probs[q];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const long long nroots = 1ll << P.k;
     double h = 0.0, l = 0.0, ab = 0.0, bad = 0.0;
     for (long long r = t; r < nroots; r += RED_THREADS) {
@@ -1089,12 +1102,33 @@ __global__ void __launch_bounds__(RED_THREADS) tor_reduce(const ProblemDesc *pro
         for (int off = NW / 2; off >= 1; off >>= 1)
             red_step<DD>(h, l, ab, bad, off);
         if (lane == 0) {
-            results[4 * q + 0] = h;
-            results[4 * q + 1] = l;
-            results[4 * q + 2] = ab;
-            results[4 * q + 3] = bad;
+            result[0] = h;
+            result[1] = l;
+            result[2] = ab;
+            result[3] = bad;
         }
     }
+}
+
+template <bool DD>
+__global__ void __launch_bounds__(RED_THREADS) tor_reduce(const ProblemDesc *probs, double *results)
+{
+    reduce_matrix<DD>(probs[blockIdx.x], results + 4 * blockIdx.x);
+}
+
+// one matrix, of the path the staging kernel gave it (a or b)
+template <bool DD>
+__global__ void __launch_bounds__(RED_THREADS) tor_reduce_one(const StageInfo *gate, int path_a, ProblemDesc a, int path_b,
+                                                              ProblemDesc b, const long long *clock, double ms_per_tick,
+                                                              double *result)
+{
+    const int path = gate->path;
+    if (threadIdx.x == 0 && (path == path_a || path == path_b))
+        result[4] = (double)(wall_clock64() - *clock) * ms_per_tick;
+    if (path == path_a)
+        reduce_matrix<DD>(a, result);
+    else if (path == path_b)
+        reduce_matrix<DD>(b, result);
 }
 
 #ifndef TOR_KERNELS_TEMPLATES_ONLY
@@ -1138,6 +1172,55 @@ hipError_t launch_main(int path, bool dd, const MainParams &p, int grid, hipStre
         else
             hipLaunchKernelGGL((tor_main<c64, CPLX_T, CPLX_B, CPLX_L, AccF64>), dim3(grid), dim3(64), 0, s, p);
     }
+    return hipGetLastError();
+}
+
+// ms per tick of the device's constant-rate clock (wall_clock64)
+static double wall_ms_per_tick()
+{
+    static const double v = [] {
+        int dev = 0, khz = 0;
+        (void)hipGetDevice(&dev);
+        (void)hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev);
+        return khz > 0 ? 1.0 / khz : 0.0;
+    }();
+    return v;
+}
+
+hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
+{
+    if (e.nrun < 1 || e.nrun > 2)
+        return hipErrorInvalidValue;
+    hipError_t err = e.stage ? launch_stage_one(e.st, e.host_info, e.counters, e.nrun, s) : launch_zero(e.counters, e.nrun, s);
+    bool reduce = false;
+    for (int i = 0; i < e.nrun && err == hipSuccess; ++i) {
+        const EvalOne::Run &r = e.run[i];
+        MainParams p{};
+        p.nprob = 1;
+        p.one = r.P;
+        p.total_items = r.P.nroots;
+        p.counter = e.counters + i;
+        p.scratch = r.scratch;
+        p.scratch_stride = r.stride;
+        p.gate = e.st.info;
+        p.gate_path = r.path;
+        p.result = r.P.nroots == 1 ? e.result : nullptr;
+        p.clock = e.clock;
+        p.ms_per_tick = wall_ms_per_tick();
+        reduce |= r.P.nroots > 1;
+        err = launch_main(r.path, e.dd, p, r.grid, s);
+    }
+    if (err != hipSuccess || !reduce)
+        return err;
+    // a path of one root has written its result: it takes no part here
+    const EvalOne::Run &a = e.run[0], &b = e.run[e.nrun - 1];
+    const int pa = a.P.nroots > 1 ? a.path : -2, pb = b.P.nroots > 1 ? b.path : -2;
+    if (e.dd)
+        hipLaunchKernelGGL((tor_reduce_one<true>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, pa, a.P, pb, b.P, e.clock,
+                           wall_ms_per_tick(), e.result);
+    else
+        hipLaunchKernelGGL((tor_reduce_one<false>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, pa, a.P, pb, b.P, e.clock,
+                           wall_ms_per_tick(), e.result);
     return hipGetLastError();
 }
 

@@ -743,6 +743,61 @@ int lane_open(LaunchLane &L, int num_cu, int first, int ncu, bool side, bool wid
     return TOR_E_DEVICE;
 }
 
+// Recovery: a matrix whose roots report numeric failures and no failed pivot
+// runs the range of its failed roots once more.  Root slots are overwritten,
+// not accumulated, so a root that runs again (or a good one inside the range)
+// leaves exactly the value a clean launch leaves, and the reduction sums the
+// slots in the same fixed order.  res: 4 doubles per descriptor, replaced for
+// the matrices that ran again (counted in runs); s_off: their slots in the
+// workspace, nslots in all from s_off[0] on; dbg_*: the debug root still to
+// fail (runs left) of matrix dbg_s.
+int rerun_failed(tor_ctx *ctx, int path, const std::vector<ProblemDesc> &descs, std::vector<double> &res,
+                 const std::vector<size_t> &s_off, long long nslots, size_t off, int grid, int dbg_s, long long dbg_root,
+                 int dbg_runs, std::vector<int> &runs)
+{
+    std::vector<int> redo;
+    for (size_t s = 0; s < descs.size(); s++)
+        if (res[4 * s + 3] == SLOT_NUMERIC)
+            redo.push_back((int)s);
+    if (redo.empty())
+        return TOR_OK;
+    std::vector<double> hs(4 * (size_t)nslots);
+    hipError_t e = hipMemcpy(hs.data(), ctx->ws + s_off[0], sizeof(double) * 4 * nslots, hipMemcpyDeviceToHost);
+    if (e != hipSuccess)
+        return hip_status(e);
+    std::vector<ProblemDesc> rd;
+    std::vector<int> rred;
+    long long item1 = 0, items = 0;
+    for (int s : redo) {
+        const long long first = (long long)(s_off[s] - s_off[0]) / (4 * (long long)sizeof(double));
+        long long lo = -1, hi = -1;
+        for (long long r = 0; r < descs[s].nroots; r++)
+            if (hs[4 * (first + r) + 3] == SLOT_NUMERIC) {
+                if (lo < 0)
+                    lo = r;
+                hi = r;
+            }
+        ProblemDesc d = descs[s];
+        d.root_begin = lo;
+        d.nroots = hi - lo + 1;
+        if (s == dbg_s && dbg_runs > 0 && dbg_root >= lo && dbg_root <= hi)
+            item1 = items + (dbg_root - lo) + 1;
+        items += d.nroots;
+        rred.push_back((int)rd.size());
+        rd.push_back(d);
+    }
+    std::vector<double> res2;
+    const int rc = run_launch(ctx, path, rd, rred, off, grid, &res2, nullptr, item1);
+    if (rc != TOR_OK)
+        return rc;
+    for (size_t i = 0; i < redo.size(); i++) {
+        for (int j = 0; j < 4; j++)
+            res[4 * (size_t)redo[i] + j] = res2[4 * i + j];
+        ++runs[redo[i]];
+    }
+    return TOR_OK;
+}
+
 // Synchronous path: all roots of every staged matrix in one launch, matrices
 // with more modes first; their root slots and the launch's own data go into
 // the workspace from byte base on.  results: 4 doubles per matrix (input
@@ -806,51 +861,9 @@ int run_recursive(tor_ctx *ctx, int path, std::vector<Mat *> &mats, std::vector<
         return rc;
     --dbg_runs;
     std::vector<int> runs(count, 1);
-    // Recovery: a matrix whose roots report numeric failures and no failed
-    // pivot runs the range of its failed roots once more.  Root slots are
-    // overwritten, not accumulated, so a root that runs again (or a good one
-    // inside the range) leaves exactly the value a clean launch leaves, and
-    // the reduction sums the slots in the same fixed order.
-    std::vector<int> redo;
-    for (int s = 0; s < count; s++)
-        if (res[4 * (size_t)s + 3] == SLOT_NUMERIC)
-            redo.push_back(s);
-    if (!redo.empty()) {
-        std::vector<double> hs(4 * (size_t)nslots);
-        hipError_t e = hipMemcpy(hs.data(), ctx->ws + s_off[0], sizeof(double) * 4 * nslots, hipMemcpyDeviceToHost);
-        if (e != hipSuccess)
-            return hip_status(e);
-        std::vector<ProblemDesc> rd;
-        std::vector<int> rred;
-        long long item1 = 0, items = 0;
-        for (int s : redo) {
-            const long long first = (long long)(s_off[s] - s_off[0]) / (4 * (long long)sizeof(double));
-            long long lo = -1, hi = -1;
-            for (long long r = 0; r < descs[s].nroots; r++)
-                if (hs[4 * (first + r) + 3] == SLOT_NUMERIC) {
-                    if (lo < 0)
-                        lo = r;
-                    hi = r;
-                }
-            ProblemDesc d = descs[s];
-            d.root_begin = lo;
-            d.nroots = hi - lo + 1;
-            if (s == dbg_s && dbg_runs > 0 && dbg_root >= lo && dbg_root <= hi)
-                item1 = items + (dbg_root - lo) + 1;
-            items += d.nroots;
-            rred.push_back((int)rd.size());
-            rd.push_back(d);
-        }
-        std::vector<double> res2;
-        rc = run_launch(ctx, path, rd, rred, off, grid, &res2, nullptr, item1);
-        if (rc != TOR_OK)
-            return rc;
-        for (size_t i = 0; i < redo.size(); i++) {
-            for (int j = 0; j < 4; j++)
-                res[4 * (size_t)redo[i] + j] = res2[4 * i + j];
-            ++runs[redo[i]];
-        }
-    }
+    rc = rerun_failed(ctx, path, descs, res, s_off, nslots, off, grid, dbg_s, dbg_root, dbg_runs, runs);
+    if (rc != TOR_OK)
+        return rc;
     if (launches) {
         launches->assign(count, 1);
         for (int s = 0; s < count; s++)
@@ -968,6 +981,165 @@ int run_staged(tor_ctx *ctx, std::vector<Mat *> &mats, const std::vector<int> &i
 bool args_ok(const tor_ctx *ctx, int n, const double *O, long ld)
 {
     return n >= 0 && n <= ctx->opt.max_n && (n == 0 || (O && ld >= 2L * n));
+}
+
+// One matrix without a host round trip between staging and the recursive
+// kernel: everything is enqueued at once, and the kernel of the path that the
+// staging kernel does not choose returns at once.  A host matrix's lower
+// triangle is packed into pinned memory, from where the staging kernel reads
+// it; the verdict and the result are written to pinned memory by the kernels.
+// *taken is false (and nothing has been done) where the general path has to
+// run: a forced root failure, a caller's workspace that does not fit every
+// path at once, a host matrix too large to be staged through LDS.
+int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, bool *taken)
+{
+    *taken = false;
+    const unsigned flags = ctx->opt.flags;
+    const bool dev_in = (flags & TOR_INPUT_DEVICE) != 0;
+    if (!launch_eval_one || ctx->dbg_runs > 0 || n == 0 || (!dev_in && n > STAGE_LDS_MODES))
+        return TOR_OK;
+    const unsigned sfl = stage_flags(flags);
+    const int n2 = 2 * n;
+    int paths[2] = {PATH_REAL, PATH_CPLX}, np = 1;
+    if (sfl & STAGE_DD)
+        paths[0] = PATH_QUAD;
+    else if (sfl & STAGE_FORCE_CPLX)
+        paths[0] = PATH_CPLX;
+    else if (dev_in)
+        np = 2;
+    else {
+        // a look at the diagonal and the first column tells almost every
+        // general matrix from a Gaussian state's (the staging kernel decides,
+        // and a wrong guess here costs a second launch)
+        auto far = [](double a, double b) { return std::fabs(a - b) > 1e-8 * (1.0 + std::fabs(a)); };
+        for (int i = 0; i < n; i++) {
+            const double *u = O + 2 * ((size_t)i * ld), *v = O + 2 * ((size_t)(n + i) * ld + n);
+            if (far(u[2 * i], v[2 * i]) || far(u[0], v[0]) || (i > 0 && far(u[1], -v[1]))) {
+                paths[0] = PATH_CPLX;
+                break;
+            }
+        }
+    }
+    // workspace: verdict, queue heads, the staged form, the root slots of
+    // either path, then a launch's own data (a later run of failed roots is
+    // an ordinary launch) and the per-wave stacks
+    const size_t oCount = 256, oForm = 512;
+    const size_t oSlots = oForm + align_up(staged_bytes(n, sfl, CPLX_R), 256);
+    EvalOne ev{};
+    size_t off = oSlots, need = 0;
+    for (int pass = 0; pass < 2; pass++)
+        for (int i = 0; i < 2; i++) {
+            // the second path's room is kept also where only the first is
+            // launched, unless the flags rule it out
+            const int path = i < np ? paths[i] : paths[0] == PATH_REAL ? PATH_CPLX : paths[0] == PATH_CPLX && !(sfl & STAGE_FORCE_CPLX) ? PATH_REAL : -1;
+            if (path < 0)
+                continue;
+            EvalOne::Run &r = ev.run[i];
+            r.path = path;
+            ProblemDesc &d = r.P;
+            d.N = std::max(n, path_R(path));
+            d.k = choose_k(ctx, d.N, path);
+            d.nroots = 1ll << d.k;
+            r.stride = std::max(wave_stack_bytes(path, d.N, d.k), 256ll);
+            const int grid = launch_grid(ctx, path, d.N);
+            r.grid = (int)std::min<long long>(grid, d.nroots);
+            if (pass == 0)
+                off = std::max(off, align_up(oSlots + sizeof(double) * 4 * (size_t)d.nroots, 256));
+            else
+                need = std::max(need, off + launch_layout(1, 1, r.stride).total(grid));
+        }
+    if (need > ctx->ws_bytes && !ctx->own_ws)
+        return TOR_OK;
+    int rc = ensure_ws(ctx, need);
+    if (rc == TOR_OK && !dev_in)
+        rc = pin_grow(ctx->hup, ctx->hup_bytes, sizeof(c64) * (size_t)n2 * n2);
+    if (rc == TOR_OK)
+        rc = pin_grow(ctx->hdown, ctx->hdown_bytes, 512);
+    if (rc != TOR_OK)
+        return rc;
+    *taken = true;
+    ev.st.n = ev.st.M = n;
+    ev.st.flags = sfl;
+    ev.st.min_cplx = CPLX_R;
+    ev.st.O = O;
+    ev.st.ld = ld;
+    if (!dev_in) {
+        // the rows as far as they are read: to the diagonal, or whole for the
+        // test of the upper triangle
+        const bool whole = (sfl & STAGE_CHECK_HERM) != 0;
+        double *h = (double *)ctx->hup;
+        for (int a = 0; a < n2; a++)
+            std::memcpy(h + 2 * (whole ? (size_t)a * n2 : (size_t)pidx(a, 0)), O + 2 * (size_t)a * (size_t)ld,
+                        sizeof(c64) * (size_t)(whole ? n2 : a + 1));
+        ev.st.O = h;
+        ev.st.ld = whole ? n2 : 0;
+    }
+    ev.st.info = (StageInfo *)ctx->ws;
+    ev.st.out = ctx->ws + oForm;
+    StageInfo *info = (StageInfo *)ctx->hdown;
+    double *res = (double *)(ctx->hdown + 256);
+    ev.stage = true;
+    ev.host_info = info;
+    ev.counters = (unsigned long long *)(ctx->ws + oCount);
+    ev.nrun = np;
+    ev.dd = ctx->opt.accum != TOR_ACCUM_FP64 || paths[0] == PATH_QUAD;
+    ev.result = res;
+    // the kernels time themselves: an event before and after the recursive
+    // kernel would put a packet of its own between it and its neighbours
+    ev.clock = (long long *)(ctx->ws + oCount) + 8;
+    for (int i = 0; i < 2; i++) {
+        EvalOne::Run &r = ev.run[i];
+        r.P.C = ev.st.out;
+        r.P.slots = (double *)(ctx->ws + oSlots);
+        r.scratch = ctx->ws + off;
+    }
+    hipError_t e = hipSetDevice(ctx->device);
+    if (e == hipSuccess)
+        e = launch_eval_one(ev, ctx->stream);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess)
+        return hip_status(e);
+    Mat m;
+    m.n = n;
+    m.N = info->N;
+    m.path = info->path;
+    m.ws_off = oForm;
+    if (info->status != 0) {
+        *out = tor_result{};
+        out->status = TOR_E_INVAL;
+        return TOR_E_INVAL;
+    }
+    int at = 0;
+    while (at < np && ev.run[at].path != m.path)
+        ++at;
+    if (at == np) {  // the other path after all
+        if (np == 2 || ev.run[1].path != m.path)
+            return TOR_E_DEVICE;
+        std::swap(ev.run[0], ev.run[1]);
+        ev.stage = false;
+        e = launch_eval_one(ev, ctx->stream);
+        if (e == hipSuccess)
+            e = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess)
+            return hip_status(e);
+        at = 0;
+    }
+    const EvalOne::Run &r = ev.run[at];
+    const float ms = (float)res[4];
+    std::vector<int> runs(1, 1);
+    double v[4] = {res[0], res[1], res[2], res[3]};
+    if (v[3] == SLOT_NUMERIC) {
+        std::vector<double> rv(v, v + 4);
+        rc = rerun_failed(ctx, m.path, std::vector<ProblemDesc>(1, r.P), rv, std::vector<size_t>(1, oSlots), r.P.nroots, off,
+                          launch_grid(ctx, m.path, m.N), -1, -1, 0, runs);
+        if (rc != TOR_OK)
+            return rc;
+        std::copy(rv.begin(), rv.end(), v);
+    }
+    fill_result(m, m.path, v, ms, out);
+    out->launches = runs[0];
+    return out->status;
 }
 
 // Evaluate the matrices in: argument checks, device staging, then one
@@ -1884,13 +2056,19 @@ int tor_eval(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out)
 {
     if (!ctx || !out)
         return TOR_E_INVAL;
+    if (!args_ok(ctx, n, O, ld))
+        return TOR_E_INVAL;
     std::lock_guard<std::mutex> g(ctx->mu);
-    std::vector<StageIn> in(1);
-    in[0].n = n;
-    in[0].O = O;
-    in[0].ld = ld;
     tor_result r{};
-    int rc = eval_many(ctx, in, &r, -1, nullptr, nullptr, ctx->opt.flags);
+    bool taken = false;
+    int rc = eval_one(ctx, n, O, ld, &r, &taken);
+    if (!taken && rc == TOR_OK) {
+        std::vector<StageIn> in(1);
+        in[0].n = n;
+        in[0].O = O;
+        in[0].ld = ld;
+        rc = eval_many(ctx, in, &r, -1, nullptr, nullptr, ctx->opt.flags);
+    }
     if (rc == TOR_E_INVAL && r.status == TOR_E_INVAL)
         return rc;
     *out = r;

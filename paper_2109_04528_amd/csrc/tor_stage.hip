@@ -39,19 +39,9 @@ namespace {
 
 constexpr double kStageU = 1.1102230246251565e-16;  // FP64 unit roundoff
 
-// (a, b), a >= b, of the t-th entry of a lower triangle numbered by rows
-__device__ inline void tri_ab(int t, int &a, int &b)
-{
-    a = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-    if (a * (a + 1) / 2 > t)
-        --a;
-    if ((a + 1) * (a + 2) / 2 <= t)
-        ++a;
-    b = t - a * (a + 1) / 2;
-}
-
-// the input seen as a 2n x 2n matrix; with lds set, its lower triangle is
-// read from there (packed by rows, pidx) instead of global memory
+// the input seen as a 2n x 2n matrix (ld 0: its lower triangle packed by rows);
+// with lds set, its lower triangle is read from there (packed by rows, pidx)
+// instead of global memory
 struct View {
     const double *O;
     long ld;
@@ -62,8 +52,11 @@ struct View {
     __device__ int row(int a) const { return sel ? (a < n ? sel[a] : sel[a - n] + M) : a; }
     __device__ c64 og(int a, int b) const
     {
-        const double *p = O + 2 * ((size_t)row(a) * (size_t)ld + (size_t)row(b));
-        return c64{p[0], p[1]};
+        // a host matrix is read across the bus, one 16-byte access per entry
+        const size_t at = ld ? (size_t)row(a) * (size_t)ld + (size_t)row(b) : (size_t)pidx(row(a), row(b));
+        typedef double dv2 __attribute__((ext_vector_type(2), aligned(8)));  // O is 8-byte aligned, no more
+        const dv2 v = *(const dv2 *)(O + 2 * at);
+        return c64{v.x, v.y};
     }
     // entry (a, b), a >= b, of O
     __device__ c64 o(int a, int b) const { return lds ? lds[pidx(a, b)] : og(a, b); }
@@ -176,16 +169,19 @@ __device__ inline void block_max(double (&v)[K], double *red)
 
 }  // namespace
 
-// lower-triangle entries staged in LDS: inputs up to n = 40 (51.8 KB);
-// larger ones are read from global memory throughout
-constexpr int STAGE_LDS_ENTRIES = NB(80);
+// lower-triangle entries staged in LDS (51.8 KB); larger inputs are read from
+// global memory throughout
+constexpr int STAGE_LDS_ENTRIES = NB(2 * STAGE_LDS_MODES);
 
+// One matrix, staged by the NT threads of a workgroup.  host_info (may be
+// null) receives a copy of the verdict.  What bounds it is latency: one pass
+// over the input (across the bus for a host matrix), one block-wide maximum,
+// one pass over the output.
 template <int NT>
-__global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
+__device__ __forceinline__ void stage_matrix(const StageDesc &D, StageInfo *host_info)
 {
     __shared__ double red[5 * (NT / 64)];
     __shared__ c64 tri[STAGE_LDS_ENTRIES];
-    const StageDesc D = descs[blockIdx.x];
     const int t = threadIdx.x;
     const int n = D.n, n2 = 2 * n;
     const bool in_lds = NB(n2) <= STAGE_LDS_ENTRIES;
@@ -210,7 +206,7 @@ __global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
         // the lower triangle only, entry q = pidx(a, b)
         for (int q = t; q < NB(n2); q += NT) {
             int a, b;
-            tri_ab(q, a, b);
+            block_ab(q, a, b);
             lower(q, a, b);
         }
     } else {
@@ -259,10 +255,10 @@ __global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
                   : path == PATH_QUAD ? max(n, QUAD_R)
                                       : max(n, D.min_cplx);
     if (t == 0) {
-        D.info->status = status;
-        D.info->path = path;
-        D.info->N = N;
-        D.info->cmax = sqrt(cmax2);
+        const StageInfo info{status, status ? -1 : path, N, 0, sqrt(cmax2)};
+        *D.info = info;
+        if (host_info)
+            *host_info = info;
     }
     if (status != 0)
         return;
@@ -272,7 +268,7 @@ __global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
         c64 *out = (c64 *)D.out;
         for (int q = t; q < NB(n2); q += NT) {
             int x, y;
-            tri_ab(q, x, y);
+            block_ab(q, x, y);
             out[pidx(x, y)] = v.c((x >> 1) + (x & 1) * n, (y >> 1) + (y & 1) * n);
         }
         return;
@@ -282,7 +278,7 @@ __global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
     for (int q = t; q < 4 * nb; q += NT) {
         const int bi = q >> 2, e = q & 3;
         int a, b;
-        tri_ab(bi, a, b);
+        block_ab(bi, a, b);
         const int x = 2 * a + (e >> 1), y = 2 * b + (e & 1);
         const int qi = 2 * N - 1 - x, qj = 2 * N - 1 - y;
         const int mi = qi >> 1, ci = qi & 1, mj = qj >> 1, cj = qj & 1;
@@ -300,6 +296,22 @@ __global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
             ((c64 *)D.out)[gpos((int)sizeof(c64), nb, bi, e)] = val;
         }
     }
+}
+
+template <int NT>
+__global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
+{
+    stage_matrix<NT>(descs[blockIdx.x], nullptr);
+}
+
+// one matrix, its descriptor a kernel argument; clears the queue heads of the
+// launches that follow
+template <int NT>
+__global__ void __launch_bounds__(NT) tor_stage_one(StageDesc D, StageInfo *host_info, unsigned long long *zero, int nzero)
+{
+    if ((int)threadIdx.x < nzero)
+        zero[threadIdx.x] = 0ull;
+    stage_matrix<NT>(D, host_info);
 }
 
 // sqrt(det(I - O)) of an M-mode O (device, leading dimension ld), by a
@@ -336,7 +348,7 @@ __global__ void __launch_bounds__(NT) tor_sqrt_det(const double *O, long ld, int
         const int r = m2 - j - 1;
         for (int q = t; q < r * (r + 1) / 2; q += NT) {
             int a, b;
-            tri_ab(q, a, b);
+            block_ab(q, a, b);
             a += j + 1;
             b += j + 1;
             const c64 la = A[(size_t)a * m2 + j], lb = A[(size_t)b * m2 + j];
@@ -361,6 +373,12 @@ hipError_t launch_stage(const StageDesc *descs, int count, hipStream_t s)
     if (count <= 0)
         return hipSuccess;
     hipLaunchKernelGGL((tor_stage<STAGE_THREADS>), dim3(count), dim3(STAGE_THREADS), 0, s, descs);
+    return hipGetLastError();
+}
+
+hipError_t launch_stage_one(const StageDesc &d, StageInfo *host_info, unsigned long long *zero, int nzero, hipStream_t s)
+{
+    hipLaunchKernelGGL((tor_stage_one<STAGE_THREADS>), dim3(1), dim3(STAGE_THREADS), 0, s, d, host_info, zero, nzero);
     return hipGetLastError();
 }
 
