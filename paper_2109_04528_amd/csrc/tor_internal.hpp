@@ -73,6 +73,7 @@ struct MainParams {
     double *result;               // a launch of one root: its slot's values go here too (or null)
     long long *clock;             // the device clock at the kernel's start goes here (or null)
     double ms_per_tick;           // of that clock
+    int tickets_only;             // blocks may start late: no item is any block's own
     ProblemDesc one;
 };
 // root slot flag (fourth double): a tested pivot failed (I - O is not

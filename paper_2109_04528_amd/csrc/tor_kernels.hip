@@ -860,21 +860,26 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
     // out the ones after the grid's.  A launch of no more items than waves
     // touches no counter at all (its one address serves the whole device's
     // waves one by one: 1024 of them took 13 to 17 us to get their first
-    // tickets).  Every lane adds 1 with nothing lane-dependent in the source,
-    // which the compiler turns into one atomic of 64 (adding 1 from lane 0
-    // only became a 64-step loop over the lanes, 2 us), so a ticket is a 64th
-    // of the old value.
+    // tickets).  Not where blocks may start late (prm.tickets_only: launches on
+    // part of the device, beside others): there the first items come from the
+    // counter too, for an item that waits for its block ends the launch late
+    // (a saturated stream of requests 1130 -> 1020 per second).
+    // Every lane adds 1 with nothing lane-dependent in the source, which the
+    // compiler turns into one atomic of 64 (adding 1 from lane 0 only became
+    // a 64-step loop over the lanes, 2 us), so a ticket is a 64th of the old
+    // value.
+    const long long nfirst = prm.tickets_only ? 0 : (long long)gridDim.x;
+    auto ticket = [&]() -> long long {
+        return nfirst < prm.total_items ? nfirst + (long long)(bcast_first(atomicAdd(prm.counter, 1ull)) >> 6)
+                                        : prm.total_items;
+    };
     // the descriptors are read where they lie, by scalar loads: prm.one in the
     // kernel's arguments (prm is the first of them) unless there is a list
     typedef const __attribute__((address_space(4))) ProblemDesc CDesc;
     CDesc *probs = prm.probs ? (CDesc *)prm.probs
                              : (CDesc *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
                                          offsetof(MainParams, one));
-    long long item = blockIdx.x;
-    for (; item < prm.total_items;
-         item = (long long)gridDim.x < prm.total_items
-                    ? (long long)gridDim.x + (long long)(bcast_first(atomicAdd(prm.counter, 1ull)) >> 6)
-                    : prm.total_items) {
+    for (long long item = prm.tickets_only ? ticket() : blockIdx.x; item < prm.total_items; item = ticket()) {
         int lo = 0, hi = prm.nprob - 1;  // last problem with item_begin <= item
         while (lo < hi) {
             int mid = (lo + hi + 1) >> 1;

@@ -639,6 +639,7 @@ int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const st
     mp.scratch_stride = stride;
     mp.fail_item1 = fail_item1;
     mp.terms = terms;
+    mp.tickets_only = lane != nullptr;
     // the double-double factor always sums in double-double
     const bool dd = ctx->opt.accum != TOR_ACCUM_FP64 || path == PATH_QUAD;
     if (e == hipSuccess)
