@@ -132,6 +132,7 @@ struct StageDesc {
     int min_cplx;      // minimum modes of the complex form
     void *out;         // the staged form (bytes: staged_bytes)
     StageInfo *info;
+    StageInfo *info2;  // a second copy of the verdict (or null)
 };
 
 // inputs up to this many modes are staged through LDS, each value read once
@@ -217,8 +218,7 @@ constexpr int FMA_PROBE_CHAINS = 16;
 // matrix is staged already (st.info holds the verdict).
 struct EvalOne {
     bool stage;
-    StageDesc st;                  // st.info: device memory
-    StageInfo *host_info;          // pinned: a copy of the verdict
+    StageDesc st;                  // st.info: device memory, st.info2: pinned
     unsigned long long *counters;  // device: a queue head per run
     int nrun;
     struct Run {
@@ -236,7 +236,7 @@ struct EvalOne {
 // takes the general path
 __attribute__((weak)) hipError_t launch_eval_one(const EvalOne &e, hipStream_t s);
 // its staging kernel (tor_stage.hip)
-hipError_t launch_stage_one(const StageDesc &d, StageInfo *host_info, unsigned long long *zero, int nzero, hipStream_t s);
+hipError_t launch_stage_one(const StageDesc &d, unsigned long long *zero, int nzero, hipStream_t s);
 
 // defined in tor_stage.hip
 hipError_t launch_stage(const StageDesc *descs, int count, hipStream_t s);

@@ -1196,7 +1196,7 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
 {
     if (e.nrun < 1 || e.nrun > 2)
         return hipErrorInvalidValue;
-    hipError_t err = e.stage ? launch_stage_one(e.st, e.host_info, e.counters, e.nrun, s) : launch_zero(e.counters, e.nrun, s);
+    hipError_t err = e.stage ? launch_stage_one(e.st, e.counters, e.nrun, s) : launch_zero(e.counters, e.nrun, s);
     bool reduce = false;
     for (int i = 0; i < e.nrun && err == hipSuccess; ++i) {
         const EvalOne::Run &r = e.run[i];

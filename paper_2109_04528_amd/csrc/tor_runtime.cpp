@@ -133,6 +133,10 @@ struct tor_ctx {
     // pinned host staging for uploads and read-backs (grown on demand)
     char *hup = nullptr, *hdown = nullptr;
     size_t hup_bytes = 0, hdown_bytes = 0;
+    char *hstate = nullptr;  // the state of a click call on its way to the device
+    size_t hstate_bytes = 0;
+    char *hout = nullptr;    // what a click_all call reads back
+    size_t hout_bytes = 0;
     TuneEntry tune[NPATH][MAX_N + 1];
     std::string arch;
 
@@ -329,35 +333,43 @@ struct StageIn {
     char *dst = nullptr;
 };
 
-// Enqueue one staging launch for in[0..count) on the context's stream: the
-// descriptors, the pattern lists and (for host inputs) the raw matrices go
-// up in one copy into the workspace from byte base on; the staged forms
-// follow them.  The kernel's status records are copied back into ctx->hdown
-// (StageInfo each, from byte 0); *end receives the first workspace byte
-// after the staging area and *down_end the first free byte of ctx->hdown.
-// stage_collect reads them after the stream has been synchronised.
-// Workspace layout of a staging launch (offsets from its base).  A host
-// matrix given several times (the same pointer, leading dimension and size,
-// as for click patterns) is uploaded once: raw_first[i] is set for the input
-// that carries each distinct copy.
+// Enqueue one staging launch for in[0..count) on the context's stream.  The
+// descriptors, the pattern lists and (for host inputs) the packed matrices are
+// written to one pinned image.  Without pattern lists the kernel reads it where
+// it is, across the bus, each value once; with them it is copied to the
+// workspace from byte base on first (every pattern reads its list and the
+// state at random).  The staged forms follow in the workspace.  The kernel
+// writes its status records to ctx->hdown (StageInfo each, from byte 0); *end
+// receives the first workspace byte after the staging area and *down_end the
+// first free byte of ctx->hdown.  stage_collect reads them after the stream
+// has been synchronised.  gate (device memory, or null) receives a copy of the
+// first one, for launches that are enqueued before it is known.
+// Layout of a staging launch: the image (descriptors, lists, matrices), and
+// the workspace (offsets from its base).  A host matrix given several times
+// (the same pointer, leading dimension and size) is there once: raw_first[i]
+// is set for the input that carries each distinct copy.
 struct StageLayout {
-    size_t b_desc = 0, b_info = 0, b_sel = 0, b_raw = 0, up_bytes = 0, total = 0;
+    size_t b_desc = 0, b_sel = 0, b_raw = 0, image = 0, up_bytes = 0, total = 0;
     std::vector<size_t> raw_off, out_off;
     std::vector<char> raw_first;
 };
+
+// a host matrix is kept whole only if its upper triangle is to be looked at
+size_t raw_entries(int rows, unsigned sflags)
+{
+    return (sflags & STAGE_CHECK_HERM) ? (size_t)rows * rows : (size_t)NB(rows);
+}
 
 StageLayout stage_layout(const std::vector<StageIn> &in, bool on_device, unsigned sflags, int min_cplx)
 {
     const int count = (int)in.size();
     StageLayout L;
     L.b_desc = align_up(sizeof(StageDesc) * count, 256);
-    L.b_info = align_up(sizeof(StageInfo) * count, 256);
     size_t nsel = 0;
     for (const StageIn &x : in)
         if (x.sel)
             nsel += (size_t)x.n;
-    L.b_sel = align_up(sizeof(int) * std::max(nsel, (size_t)1), 256);
-    // raw inputs: one compact copy per distinct host matrix
+    L.b_sel = align_up(sizeof(int) * nsel, 256);
     L.raw_off.assign(count, 0);
     L.raw_first.assign(count, 0);
     std::map<std::tuple<const double *, long, int>, size_t> seen;
@@ -371,11 +383,12 @@ StageLayout stage_layout(const std::vector<StageIn> &in, bool on_device, unsigne
             if (it == seen.end()) {
                 it = seen.emplace(key, L.b_raw).first;
                 L.raw_first[i] = 1;
-                L.b_raw += align_up(sizeof(c64) * (size_t)rows * rows, 256);
+                L.b_raw += align_up(sizeof(c64) * raw_entries(rows, sflags), 256);
             }
             L.raw_off[i] = it->second;
         }
-    L.up_bytes = L.b_desc + L.b_info + L.b_sel + L.b_raw;
+    L.image = L.b_desc + L.b_sel + L.b_raw;
+    L.up_bytes = nsel ? L.image : 0;
     size_t out_bytes = 0;
     L.out_off.assign(count, 0);
     for (int i = 0; i < count; i++)
@@ -387,8 +400,24 @@ StageLayout stage_layout(const std::vector<StageIn> &in, bool on_device, unsigne
     return L;
 }
 
+// A host matrix's rows as the staging kernel takes them: to the diagonal,
+// packed (leading dimension 0), or whole; returns the leading dimension.
+long pack_rows(char *dst, const double *O, long ld, int rows, unsigned sflags)
+{
+    const bool whole = (sflags & STAGE_CHECK_HERM) != 0;
+    for (int a = 0; a < rows; a++)
+        std::memcpy(dst + sizeof(c64) * (whole ? (size_t)a * rows : (size_t)pidx(a, 0)), O + 2 * (size_t)a * (size_t)ld,
+                    sizeof(c64) * (size_t)(whole ? rows : a + 1));
+    return whole ? rows : 0;
+}
+
+// bytes kept free behind the image for a launch of one matrix that is enqueued
+// before the staging kernel has read the image (run_launch's hup_at)
+constexpr size_t LAUNCH_UP_SPARE = 1024;
+
 int stage_enqueue(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, unsigned sflags, int min_cplx,
-                  size_t base, std::vector<Mat> &mats, size_t *end, size_t *down_end, hipStream_t stream = nullptr)
+                  size_t base, std::vector<Mat> &mats, size_t *end, size_t *down_end, hipStream_t stream = nullptr,
+                  StageInfo *gate = nullptr)
 {
     if (!stream)
         stream = ctx->stream;
@@ -399,21 +428,22 @@ int stage_enqueue(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, 
     if (count == 0)
         return TOR_OK;
     const StageLayout L = stage_layout(in, on_device, sflags, min_cplx);
-    const size_t b_desc = L.b_desc, b_info = L.b_info, b_sel = L.b_sel, up_bytes = L.up_bytes;
     const std::vector<size_t> &raw_off = L.raw_off, &out_off = L.out_off;
+    const size_t b_info = align_up(sizeof(StageInfo) * count, 256);
     // device inputs that live in the workspace must already fit (growing
     // it would move them)
     int rc = ensure_ws_keep(ctx, base + L.total, base);
     if (rc == TOR_OK)
-        rc = pin_grow(ctx->hup, ctx->hup_bytes, up_bytes);
+        rc = pin_grow(ctx->hup, ctx->hup_bytes, L.image + LAUNCH_UP_SPARE);
     if (rc == TOR_OK)  // 256 spare bytes for a caller's own read-back
         rc = pin_grow(ctx->hdown, ctx->hdown_bytes, b_info + 256);
     if (rc != TOR_OK)
         return rc;
     char *dbase = ctx->ws + base;
     char *h = ctx->hup;
+    char *image = L.up_bytes ? dbase : h;  // where the kernel reads it
     StageDesc *hd = (StageDesc *)h;
-    int *hsel = (int *)(h + b_desc + b_info);
+    int *hsel = (int *)(h + L.b_desc);
     size_t sel_at = 0;
     struct RawCopy {
         char *dst;
@@ -429,19 +459,20 @@ int stage_enqueue(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, 
         d.M = x.sel ? x.M : x.n;
         d.flags = sflags;
         d.min_cplx = min_cplx;
-        d.info = (StageInfo *)(dbase + b_desc) + i;
+        d.info = (StageInfo *)ctx->hdown + i;
+        d.info2 = i == 0 ? gate : nullptr;
         d.out = x.dst ? (void *)x.dst : (void *)(dbase + out_off[i]);
         if (x.sel) {
             std::memcpy(hsel + sel_at, x.sel, sizeof(int) * (size_t)x.n);
-            d.sel = (const int *)(dbase + b_desc + b_info) + sel_at;
+            d.sel = (const int *)(image + L.b_desc) + sel_at;
             sel_at += (size_t)x.n;
         }
         const int rows = 2 * d.M;
         if (rows > 0 && !on_device) {
             if (L.raw_first[i])
-                copies.push_back(RawCopy{h + b_desc + b_info + b_sel + raw_off[i], x.O, x.ld, rows});
-            d.O = (const double *)(dbase + b_desc + b_info + b_sel + raw_off[i]);
-            d.ld = rows;
+                copies.push_back(RawCopy{h + L.b_desc + L.b_sel + raw_off[i], x.O, x.ld, rows});
+            d.O = (const double *)(image + L.b_desc + L.b_sel + raw_off[i]);
+            d.ld = (sflags & STAGE_CHECK_HERM) ? rows : 0;
         } else {
             d.O = x.O;
             d.ld = x.ld;
@@ -454,12 +485,8 @@ int stage_enqueue(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, 
     // compact the host inputs into the pinned image, on a few threads for a
     // large batch
     auto do_copies = [&](size_t first, size_t step) {
-        for (size_t c = first; c < copies.size(); c += step) {
-            const RawCopy &rc_ = copies[c];
-            for (int r = 0; r < rc_.rows; r++)
-                std::memcpy(rc_.dst + sizeof(c64) * (size_t)r * rc_.rows, rc_.src + 2 * (size_t)r * (size_t)rc_.ld,
-                            sizeof(c64) * (size_t)rc_.rows);
-        }
+        for (size_t c = first; c < copies.size(); c += step)
+            (void)pack_rows(copies[c].dst, copies[c].src, copies[c].ld, copies[c].rows, sflags);
     };
     const size_t nthr = L.b_raw > ((size_t)4 << 20) && copies.size() >= 16
                             ? std::min<size_t>(8, std::max(1u, std::thread::hardware_concurrency()))
@@ -474,13 +501,10 @@ int stage_enqueue(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, 
             th.join();
     }
     hipError_t e = hipSetDevice(ctx->device);
-    // the infos' bytes are part of the copy (their values do not matter)
+    if (e == hipSuccess && L.up_bytes)
+        e = hipMemcpyAsync(dbase, h, L.up_bytes, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(dbase, h, up_bytes, hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-        e = launch_stage((const StageDesc *)dbase, count, stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ctx->hdown, dbase + b_desc, sizeof(StageInfo) * count, hipMemcpyDeviceToHost, stream);
+        e = launch_stage((const StageDesc *)image, count, stream);
     if (e != hipSuccess)
         return hip_status(e);
     *end = base + L.total;
@@ -516,6 +540,28 @@ int stage_sync(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, uns
 }
 
 
+// click_all outputs up to this size that go to host memory are written by the
+// kernel across the bus into pinned memory and copied from there; larger ones
+// go through device memory (a pinned buffer of that size would stay with the
+// context).
+constexpr size_t CLICK_PINNED_BYTES = 8u << 20;
+
+// The M-mode state of a click call in device memory: the caller's, or a copy
+// of its rows at the workspace's start (one copy from pinned memory: the
+// caller's rows one by one took 15 us each).  O and ld are replaced.
+int upload_state(tor_ctx *ctx, int M, unsigned sflags, const double *&O, long &ld)
+{
+    if ((ctx->opt.flags & TOR_INPUT_DEVICE) || M == 0)
+        return TOR_OK;
+    const size_t bytes = sizeof(c64) * raw_entries(2 * M, sflags);
+    const int rc = pin_grow(ctx->hstate, ctx->hstate_bytes, bytes);
+    if (rc != TOR_OK)
+        return rc;
+    ld = pack_rows(ctx->hstate, O, ld, 2 * M, sflags);
+    O = (const double *)ctx->ws;
+    return hip_status(hipMemcpyAsync(ctx->ws, ctx->hstate, bytes, hipMemcpyHostToDevice, ctx->stream));
+}
+
 // Bytes of one persistent wave's stack for a matrix of N modes split at
 // depth k (tslot_off): the root node, the tier-A slots, the determinants.
 long long wave_stack_bytes(int path, int N, int k)
@@ -525,12 +571,13 @@ long long wave_stack_bytes(int path, int N, int k)
 }
 
 // Workspace bytes a launch needs after its matrices and slots: descriptors,
-// reduction descriptors, queue counter, results, per-wave stacks (stride:
-// the largest wave_stack_bytes of the launch's matrices).
+// reduction descriptors, queue counter, per-wave stacks (stride: the largest
+// wave_stack_bytes of the launch's matrices).  The results go straight to
+// pinned memory.
 struct LaunchLayout {
-    size_t b_probs, b_red, b_counter, b_res;
+    size_t b_probs, b_red, b_counter;
     long long stride;
-    size_t total(int grid) const { return b_probs + b_red + b_counter + b_res + (size_t)stride * grid; }
+    size_t total(int grid) const { return b_probs + b_red + b_counter + (size_t)stride * grid; }
 };
 
 LaunchLayout launch_layout(int count, int nred, long long stride)
@@ -539,7 +586,6 @@ LaunchLayout launch_layout(int count, int nred, long long stride)
     L.b_probs = align_up(sizeof(ProblemDesc) * std::max(count, 1), 256);
     L.b_red = align_up(sizeof(ProblemDesc) * std::max(nred, 1), 256);
     L.b_counter = 256;
-    L.b_res = align_up(sizeof(double) * 4 * std::max(nred, 1), 256);
     L.stride = std::max(stride, 256ll);
     return L;
 }
@@ -570,17 +616,20 @@ int lane_ws(LaunchLane &L, size_t bytes)
 // One persistent launch over the root ranges in descs (C, slots, N, k,
 // root_begin, nroots filled in), followed by the reduction of the matrices
 // listed in reduce (indices into descs, or none), into results (4 doubles
-// each).  The workspace from byte ws_off on holds descriptors, counter,
-// results and the per-wave tier-A stacks.  When ws_off > 0 the bytes below it
+// each).  The workspace from byte ws_off on holds descriptors, counter and
+// the per-wave tier-A stacks.  When ws_off > 0 the bytes below it
 // hold data the descriptors point to, and the caller has already sized the
 // workspace (a reallocation here would move that data).
 // With a lane, the launch goes to the lane's current stream, its workspace
 // and the pinned buffers of its current slot, and the call returns once it
-// is enqueued: the slot's done event follows the read-back of the results,
-// which lane_collect then takes.
+// is enqueued: the slot's done event follows the reduction into the slot's
+// pinned buffer, which lane_collect then reads.  gate: the launch is enqueued
+// before the staging kernel's verdict is known, runs only if that is `path`,
+// and its descriptors go to byte hup_at of the pinned buffer, behind what the
+// staging kernel has still to read.
 int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const std::vector<int> &reduce,
                size_t ws_off, int grid, std::vector<double> *results, float *ms, long long fail_item1 = 0,
-               double *terms = nullptr, LaunchLane *lane = nullptr)
+               double *terms = nullptr, LaunchLane *lane = nullptr, const StageInfo *gate = nullptr, size_t hup_at = 0)
 {
     const int count = (int)descs.size();
     long long total = 0, stack = 0;
@@ -610,26 +659,29 @@ int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const st
     char *dProbs = (lane ? lane->ws : ctx->ws) + ws_off;
     char *dRed = dProbs + Lo.b_probs;
     unsigned long long *dCounter = (unsigned long long *)(dRed + Lo.b_red);
-    double *dRes = (double *)((char *)dCounter + Lo.b_counter);
-    char *dScr = (char *)dRes + Lo.b_res;
+    char *dScr = (char *)dCounter + Lo.b_counter;
     const long long stride = Lo.stride;
     // descriptors and reduction descriptors at their exact byte offsets and
     // the zeroed queue counter after them: one copy from pinned memory (the
     // previous use of the buffer has been synchronised)
     const size_t up = Lo.b_probs + Lo.b_red + sizeof(unsigned long long);
-    rc = pin_grow(hup, hup_bytes, up);
-    if (rc == TOR_OK)
+    if (hup_at > 0)  // what lies below is still to be read, so nothing may move
+        rc = hup_at + up <= hup_bytes && sizeof(double) * 4 * (size_t)nred <= hdown_bytes ? TOR_OK : TOR_E_NOMEM;
+    else
+        rc = pin_grow(hup, hup_bytes, up);
+    if (rc == TOR_OK && hup_at == 0)
         rc = pin_grow(hdown, hdown_bytes, sizeof(double) * 4 * (size_t)std::max(nred, 1));
     if (rc != TOR_OK)
         return rc;
-    std::memset(hup, 0, up);
-    std::memcpy(hup, descs.data(), sizeof(ProblemDesc) * count);
+    char *const image = hup + hup_at;
+    std::memset(image, 0, up);
+    std::memcpy(image, descs.data(), sizeof(ProblemDesc) * count);
     if (nred)
-        std::memcpy(hup + Lo.b_probs, red.data(), sizeof(ProblemDesc) * nred);
+        std::memcpy(image + Lo.b_probs, red.data(), sizeof(ProblemDesc) * nred);
 
     hipError_t e = hipSetDevice(ctx->device);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(dProbs, hup, up, hipMemcpyHostToDevice, stream);
+        e = hipMemcpyAsync(dProbs, image, up, hipMemcpyHostToDevice, stream);
     MainParams mp{};
     mp.probs = (const ProblemDesc *)dProbs;
     mp.nprob = count;
@@ -640,6 +692,8 @@ int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const st
     mp.fail_item1 = fail_item1;
     mp.terms = terms;
     mp.tickets_only = lane != nullptr;
+    mp.gate = gate;
+    mp.gate_path = path;
     // the double-double factor always sums in double-double
     const bool dd = ctx->opt.accum != TOR_ACCUM_FP64 || path == PATH_QUAD;
     if (e == hipSuccess)
@@ -652,11 +706,8 @@ int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const st
     if (e == hipSuccess)
         e = hipEventRecord(ev1, stream);  // device_ms: the main kernel alone
     const double *hres = (const double *)hdown;
-    if (e == hipSuccess && nred > 0) {
-        e = launch_reduce((const ProblemDesc *)dRed, nred, dRes, dd, stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(hdown, dRes, sizeof(double) * 4 * nred, hipMemcpyDeviceToHost, stream);
-    }
+    if (e == hipSuccess && nred > 0)
+        e = launch_reduce((const ProblemDesc *)dRed, nred, (double *)hdown, dd, stream);
     if (lane) {
         if (e == hipSuccess)
             e = hipEventRecord(lane->done[sl], stream);
@@ -1053,7 +1104,7 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
         return TOR_OK;
     int rc = ensure_ws(ctx, need);
     if (rc == TOR_OK && !dev_in)
-        rc = pin_grow(ctx->hup, ctx->hup_bytes, sizeof(c64) * (size_t)n2 * n2);
+        rc = pin_grow(ctx->hup, ctx->hup_bytes, sizeof(c64) * raw_entries(n2, sfl));
     if (rc == TOR_OK)
         rc = pin_grow(ctx->hdown, ctx->hdown_bytes, 512);
     if (rc != TOR_OK)
@@ -1065,22 +1116,15 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
     ev.st.O = O;
     ev.st.ld = ld;
     if (!dev_in) {
-        // the rows as far as they are read: to the diagonal, or whole for the
-        // test of the upper triangle
-        const bool whole = (sfl & STAGE_CHECK_HERM) != 0;
-        double *h = (double *)ctx->hup;
-        for (int a = 0; a < n2; a++)
-            std::memcpy(h + 2 * (whole ? (size_t)a * n2 : (size_t)pidx(a, 0)), O + 2 * (size_t)a * (size_t)ld,
-                        sizeof(c64) * (size_t)(whole ? n2 : a + 1));
-        ev.st.O = h;
-        ev.st.ld = whole ? n2 : 0;
+        ev.st.O = (const double *)ctx->hup;
+        ev.st.ld = pack_rows(ctx->hup, O, ld, n2, sfl);
     }
     ev.st.info = (StageInfo *)ctx->ws;
     ev.st.out = ctx->ws + oForm;
     StageInfo *info = (StageInfo *)ctx->hdown;
     double *res = (double *)(ctx->hdown + 256);
     ev.stage = true;
-    ev.host_info = info;
+    ev.st.info2 = info;
     ev.counters = (unsigned long long *)(ctx->ws + oCount);
     ev.nrun = np;
     ev.dd = ctx->opt.accum != TOR_ACCUM_FP64 || paths[0] == PATH_QUAD;
@@ -1791,7 +1835,9 @@ int eval_static(tor_ctx *ctx, char *base, int n, const double *O, long ld, tor_r
     // host memory the caller or this frame owns, both alive until the
     // synchronisations below
     hipError_t e = hipSetDevice(ctx->device);
-    if (e == hipSuccess && dRaw)
+    if (e == hipSuccess && dRaw && ld == n2)  // one copy: rows one by one take about 15 us each
+        e = hipMemcpyAsync(dRaw, O, sizeof(c64) * (size_t)n2 * n2, hipMemcpyHostToDevice, ctx->stream);
+    else if (e == hipSuccess && dRaw)
         e = hipMemcpy2DAsync(dRaw, sizeof(c64) * n2, O, sizeof(c64) * (size_t)ld, sizeof(c64) * n2, n2,
                              hipMemcpyHostToDevice, ctx->stream);
     StageDesc d{};
@@ -2028,6 +2074,10 @@ void tor_destroy(tor_ctx *ctx)
             (void)hipHostFree(ctx->hup);
         if (ctx->hdown)
             (void)hipHostFree(ctx->hdown);
+        if (ctx->hstate)
+            (void)hipHostFree(ctx->hstate);
+        if (ctx->hout)
+            (void)hipHostFree(ctx->hout);
         if (ctx->ev0)
             (void)hipEventDestroy(ctx->ev0);
         if (ctx->ev1)
@@ -2161,19 +2211,13 @@ int tor_click_probs(tor_ctx *ctx, int M, const double *O, long ld, int count, co
     if (rc != TOR_OK)
         return rc;
     hipError_t e = hipSetDevice(ctx->device);
-    const double *dO = O;
-    long dld = ld;
-    if (!dev && M > 0) {
-        e = hipMemcpy2DAsync(ctx->ws, sizeof(c64) * m2, O, sizeof(c64) * (size_t)ld, sizeof(c64) * m2, m2,
-                             hipMemcpyHostToDevice, ctx->stream);
-        dO = (const double *)ctx->ws;
-        dld = m2;
-    }
-    double *dDet = (double *)(ctx->ws + bO + bScr);
-    if (e == hipSuccess && M > 0)
-        e = launch_sqrt_det(dO, dld, M, (c64 *)(ctx->ws + bO), dDet, ctx->stream);
     if (e != hipSuccess)
         return hip_status(e);
+    const double *dO = O;
+    long dld = ld;
+    rc = upload_state(ctx, M, sfl, dO, dld);
+    if (rc != TOR_OK)
+        return rc;
     for (int i = 0; i < count; i++) {
         in[i].O = dO;
         in[i].ld = dld;
@@ -2181,19 +2225,20 @@ int tor_click_probs(tor_ctx *ctx, int M, const double *O, long ld, int count, co
     std::vector<Mat> mats;
     size_t end = 0, down = 0;
     rc = stage_enqueue(ctx, in, true, sfl, CPLX_R, base, mats, &end, &down);
-    if (rc != TOR_OK)
-        return rc;
-    // stage_enqueue leaves 256 spare bytes after the status records (a copy into
-    // the buffer is pending, so it must not be regrown here)
+    // stage_enqueue leaves 256 spare bytes after the status records (the
+    // staging kernel writes to the buffer, so it must not be regrown here)
     const size_t det_at = align_up(down, 16);
-    if (det_at + 2 * sizeof(double) > ctx->hdown_bytes)
-        return TOR_E_NOMEM;
+    if (rc == TOR_OK && det_at + 2 * sizeof(double) > ctx->hdown_bytes)
+        rc = TOR_E_NOMEM;
+    if (rc != TOR_OK) {
+        (void)hipStreamSynchronize(ctx->stream);  // the state's copy
+        return rc;
+    }
     double *hDet = (double *)(ctx->hdown + det_at);
     hDet[0] = 1.0;
     hDet[1] = 0.0;
-    e = hipSuccess;
     if (M > 0)
-        e = hipMemcpyAsync(hDet, dDet, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
+        e = launch_sqrt_det(dO, dld, M, (c64 *)(ctx->ws + bO), hDet, ctx->stream);
     if (e == hipSuccess)
         e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess)
@@ -2277,73 +2322,71 @@ int tor_click_all(tor_ctx *ctx, int M, const double *O, long ld, double *probs, 
     const bool dev = (ctx->opt.flags & TOR_INPUT_DEVICE) != 0;
     const size_t bO = dev ? 0 : align_up(sizeof(c64) * (size_t)m2 * m2, 256);
     const size_t bScr = align_up(sizeof(c64) * (size_t)m2 * m2, 256);
-    const size_t base = bO + bScr + 256;
+    const size_t oGate = bO + bScr + 256, base = oGate + 256;
     std::vector<StageIn> in(1);
     in[0].n = M;
     in[0].M = M;
     const unsigned sfl = stage_flags(ctx->opt.flags);
-    int rc = ensure_ws_keep(ctx, base + stage_layout(in, true, sfl, CPLX_R).total, 0);
-    if (rc != TOR_OK)
-        return rc;
-    hipError_t e = hipSetDevice(ctx->device);
-    const double *dO = O;
-    long dld = ld;
-    if (e == hipSuccess && !dev) {
-        e = hipMemcpy2DAsync(ctx->ws, sizeof(c64) * m2, O, sizeof(c64) * (size_t)ld, sizeof(c64) * m2, m2,
-                             hipMemcpyHostToDevice, ctx->stream);
-        dO = (const double *)ctx->ws;
-        dld = m2;
-    }
-    double *dDet = (double *)(ctx->ws + bO + bScr);
-    if (e == hipSuccess)
-        e = launch_sqrt_det(dO, dld, M, (c64 *)(ctx->ws + bO), dDet, ctx->stream);
-    if (e != hipSuccess)
-        return hip_status(e);
-    in[0].O = dO;
-    in[0].ld = dld;
-    std::vector<Mat> mats;
-    size_t end = 0, down = 0;
-    rc = stage_enqueue(ctx, in, true, sfl, CPLX_R, base, mats, &end, &down);
-    if (rc != TOR_OK)
-        return rc;
-    const size_t det_at = align_up(down, 16);
-    if (det_at + 2 * sizeof(double) > ctx->hdown_bytes)
-        return TOR_E_NOMEM;
-    double *hDet = (double *)(ctx->hdown + det_at);
-    e = hipMemcpyAsync(hDet, dDet, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess)
-        return hip_status(e);
-    stage_collect(ctx, mats);
-    if (hDet[1] != 0.0 || !(hDet[0] > 0.0))
-        return TOR_E_NOT_PD;
-    if (mats[0].status != TOR_OK)
-        return mats[0].status;
-    if (mats[0].path != PATH_REAL)
-        return TOR_E_INVAL;  // O lacks the Gaussian-state block structure
-    const int N = mats[0].N;
+    // The workspace is sized before anything is enqueued.  After the staged
+    // matrix: root slots, the 2^N terms, their subset sums, staging arrays
+    // for large outputs that go to the host (none with TOR_OUTPUT_DEVICE;
+    // small ones are written straight to pinned memory), then what run_launch
+    // needs.  The real path is the only one that stores terms, so its size and
+    // depth are known before the staging kernel's verdict: the recursive
+    // kernel is enqueued behind it and returns at once without that path.
+    const StageLayout SL = stage_layout(in, true, sfl, CPLX_R);
+    const size_t end = base + SL.total;
+    const int N = std::max(M, REAL_R);
     const int k = choose_k(ctx, N, PATH_REAL);
-    // after the staged matrix: root slots, the 2^N terms, their subset sums,
-    // staging arrays for the outputs that go to the host (none with
-    // TOR_OUTPUT_DEVICE), then what run_launch needs
     const long long nS = 1ll << N, nP = 1ll << M;
     const size_t oSlots = align_up(end, 256);
     const size_t oTerms = align_up(oSlots + sizeof(double) * 4 * ((size_t)1 << k), 256);
     const size_t oG = align_up(oTerms + sizeof(double) * (size_t)nS, 256);
     const size_t oOut = align_up(oG + sizeof(ddr) * (size_t)nS, 256);
-    const int nstage = dev_out ? 0 : (probs ? 1 : 0) + (tor_hi ? 2 : 0);
-    const size_t off = align_up(oOut + nstage * sizeof(double) * (size_t)nP, 256);
+    const size_t out_bytes = dev_out ? 0 : ((probs ? 1 : 0) + (tor_hi ? 2 : 0)) * sizeof(double) * (size_t)nP;
+    const bool pinned_out = out_bytes > 0 && out_bytes <= CLICK_PINNED_BYTES;
+    const size_t off = align_up(oOut + (pinned_out ? 0 : out_bytes), 256);
     const long long stack = wave_stack_bytes(PATH_REAL, N, k);
     const int fit = std::max(1, std::min(main_store_occupancy(), ctx->fit[PATH_REAL]));
     const int grid = ctx->num_cu * fit;
-    rc = ensure_ws_keep(ctx, off + launch_layout(1, 1, stack).total(grid), end);
+    int rc = ensure_ws_keep(ctx, off + launch_layout(1, 1, stack).total(grid), 0);
     if (rc != TOR_OK)
         return rc;
+    hipError_t e = hipSetDevice(ctx->device);
+    if (e != hipSuccess)
+        return hip_status(e);
+    const double *dO = O;
+    long dld = ld;
+    rc = upload_state(ctx, M, sfl, dO, dld);
+    if (rc != TOR_OK)
+        return rc;
+    double *dDet = (double *)(ctx->ws + bO + bScr);
+    StageInfo *gate = (StageInfo *)(ctx->ws + oGate);
+    in[0].O = dO;
+    in[0].ld = dld;
+    std::vector<Mat> mats;
+    size_t got_end = 0, down = 0;
+    rc = stage_enqueue(ctx, in, true, sfl, CPLX_R, base, mats, &got_end, &down, nullptr, gate);
+    // pinned, in a buffer of its own (run_launch uses the other two):
+    // sqrt(det), the whole state's sum, the verdict, then the outputs
+    if (rc == TOR_OK && (rc = pin_grow(ctx->hout, ctx->hout_bytes, 256 + (pinned_out ? out_bytes : 0))) == TOR_OK)
+        rc = hip_status(launch_sqrt_det(dO, dld, M, (c64 *)(ctx->ws + bO), dDet, ctx->stream));
+    if (rc != TOR_OK) {
+        (void)hipStreamSynchronize(ctx->stream);  // the state's copy
+        return rc;
+    }
+    double *hDet = (double *)ctx->hout;
+    ddr *hFull = (ddr *)(ctx->hout + 16);
+    StageInfo *hInfo = (StageInfo *)(ctx->hout + 64);
+    e = hipMemcpyAsync(hDet, dDet, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(hInfo, gate, sizeof(StageInfo), hipMemcpyDeviceToHost, ctx->stream);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(ctx->stream);
+        return hip_status(e);
+    }
     double *dTerms = (double *)(ctx->ws + oTerms);
     ddr *dG = (ddr *)(ctx->ws + oG);
-    double *dP = (double *)(ctx->ws + oOut), *dH = dP + (probs ? nP : 0), *dL = dH + nP;
-    dDet = (double *)(ctx->ws + bO + bScr);  // the workspace may have moved
     std::vector<ProblemDesc> descs(1);
     ProblemDesc &d = descs[0];
     d.C = mat_ptr(ctx, mats[0]);
@@ -2354,9 +2397,18 @@ int tor_click_all(tor_ctx *ctx, int M, const double *O, long ld, double *probs, 
     d.nroots = 1ll << k;
     std::vector<double> res;
     float ms_main = 0.f, ms_zeta = 0.f;
-    rc = run_launch(ctx, PATH_REAL, descs, std::vector<int>{0}, off, grid, &res, &ms_main, 0, dTerms);
-    if (rc != TOR_OK)
+    rc = run_launch(ctx, PATH_REAL, descs, std::vector<int>{0}, off, grid, &res, &ms_main, 0, dTerms, nullptr, gate,
+                    align_up(SL.image, 256));
+    if (rc != TOR_OK) {
+        (void)hipStreamSynchronize(ctx->stream);
         return rc;
+    }
+    if (hDet[1] != 0.0 || !(hDet[0] > 0.0))
+        return TOR_E_NOT_PD;
+    if (hInfo->status != 0 || hInfo->path != PATH_REAL)
+        return TOR_E_INVAL;  // bad values, or O lacks the Gaussian-state block structure
+    mats[0].path = PATH_REAL;
+    mats[0].N = N;
     if (res[3] >= SLOT_NOT_PD)
         return TOR_E_NOT_PD;
     if (res[3] > 0.0)
@@ -2364,37 +2416,42 @@ int tor_click_all(tor_ctx *ctx, int M, const double *O, long ld, double *probs, 
     e = hipEventRecord(ctx->ev0, ctx->stream);
     if (e == hipSuccess)
         e = launch_zeta(dTerms, dG, N, ctx->stream);
-    // where the kernel writes: the caller's device arrays, or the workspace
-    // (then copied to the caller's host arrays)
-    double *pP = probs ? (dev_out ? probs : dP) : nullptr;
-    double *pH = tor_hi ? (dev_out ? tor_hi : dH) : nullptr;
-    double *pL = tor_lo ? (dev_out ? tor_lo : dL) : nullptr;
+    // where the kernel writes: the caller's device arrays, pinned memory, or
+    // the workspace (the latter two then copied to the caller's host arrays)
+    double *stage = pinned_out ? (double *)(ctx->hout + 256) : (double *)(ctx->ws + oOut);
+    double *pP = probs ? (dev_out ? probs : stage) : nullptr;
+    double *pH = tor_hi ? (dev_out ? tor_hi : stage + (probs ? nP : 0)) : nullptr;
+    double *pL = tor_lo ? (dev_out ? tor_lo : stage + (probs ? nP : 0) + nP) : nullptr;
     if (e == hipSuccess && (pP || pH))
         e = launch_click_out(dG, N, M, dDet, pP, pH, pL, ctx->stream);
     if (e == hipSuccess)
         e = hipEventRecord(ctx->ev1, ctx->stream);
-    if (e == hipSuccess && probs && !dev_out)
-        e = hipMemcpyAsync(probs, dP, sizeof(double) * nP, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess && tor_hi && !dev_out)
-        e = hipMemcpyAsync(tor_hi, dH, sizeof(double) * nP, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess && tor_lo && !dev_out)
-        e = hipMemcpyAsync(tor_lo, dL, sizeof(double) * nP, hipMemcpyDeviceToHost, ctx->stream);
+    struct Out {
+        double *to;
+        const double *from;
+    };
+    const Out outs[3] = {{probs, pP}, {tor_hi, pH}, {tor_lo, pL}};
+    for (const Out &o : outs)
+        if (e == hipSuccess && o.to && !dev_out && !pinned_out)
+            e = hipMemcpyAsync(o.to, o.from, sizeof(double) * nP, hipMemcpyDeviceToHost, ctx->stream);
     // the whole state's Tor for out: the subset sum of the pattern of every
     // mode (index bit N-1-q for mode q: the top M bits), with the sign
     // (-1)^(N-M) that turns a subset sum into a Torontonian
-    ddr full{0.0, 0.0};
     if (e == hipSuccess && out)
-        e = hipMemcpyAsync(&full, dG + ((nP - 1) << (N - M)), sizeof(ddr), hipMemcpyDeviceToHost, ctx->stream);
+        e = hipMemcpyAsync(hFull, dG + ((nP - 1) << (N - M)), sizeof(ddr), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess)
         e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess)
         return hip_status(e);
+    for (const Out &o : outs)
+        if (o.to && pinned_out)
+            std::memcpy(o.to, o.from, sizeof(double) * nP);
     (void)hipEventElapsedTime(&ms_zeta, ctx->ev0, ctx->ev1);
     if (out) {
         // the result of the whole state (every mode clicks), with the sum of
         // |t| over all subsets and the device time of both steps
         const double sg = ((N - M) & 1) ? -1.0 : 1.0;
-        const double r[4] = {sg * full.hi, sg * full.lo, res[2], 0.0};
+        const double r[4] = {sg * hFull->hi, sg * hFull->lo, res[2], 0.0};
         fill_result(mats[0], PATH_REAL, r, ms_main + ms_zeta, out);
     }
     return TOR_OK;

@@ -173,12 +173,11 @@ __device__ inline void block_max(double (&v)[K], double *red)
 // global memory throughout
 constexpr int STAGE_LDS_ENTRIES = NB(2 * STAGE_LDS_MODES);
 
-// One matrix, staged by the NT threads of a workgroup.  host_info (may be
-// null) receives a copy of the verdict.  What bounds it is latency: one pass
+// One matrix, staged by the NT threads of a workgroup.  What bounds it is latency: one pass
 // over the input (across the bus for a host matrix), one block-wide maximum,
 // one pass over the output.
 template <int NT>
-__device__ __forceinline__ void stage_matrix(const StageDesc &D, StageInfo *host_info)
+__device__ __forceinline__ void stage_matrix(const StageDesc &D)
 {
     __shared__ double red[5 * (NT / 64)];
     __shared__ c64 tri[STAGE_LDS_ENTRIES];
@@ -257,8 +256,8 @@ __device__ __forceinline__ void stage_matrix(const StageDesc &D, StageInfo *host
     if (t == 0) {
         const StageInfo info{status, status ? -1 : path, N, 0, sqrt(cmax2)};
         *D.info = info;
-        if (host_info)
-            *host_info = info;
+        if (D.info2)
+            *D.info2 = info;
     }
     if (status != 0)
         return;
@@ -301,24 +300,81 @@ __device__ __forceinline__ void stage_matrix(const StageDesc &D, StageInfo *host
 template <int NT>
 __global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
 {
-    stage_matrix<NT>(descs[blockIdx.x], nullptr);
+    stage_matrix<NT>(descs[blockIdx.x]);
 }
 
 // one matrix, its descriptor a kernel argument; clears the queue heads of the
 // launches that follow
 template <int NT>
-__global__ void __launch_bounds__(NT) tor_stage_one(StageDesc D, StageInfo *host_info, unsigned long long *zero, int nzero)
+__global__ void __launch_bounds__(NT) tor_stage_one(StageDesc D, unsigned long long *zero, int nzero)
 {
     if ((int)threadIdx.x < nzero)
         zero[threadIdx.x] = 0ull;
-    stage_matrix<NT>(D, host_info);
+    stage_matrix<NT>(D);
 }
 
-// sqrt(det(I - O)) of an M-mode O (device, leading dimension ld), by a
-// Cholesky factorisation of the Hermitian completion of the lower triangle
-// of C = I - O in the caller's scratch (2M x 2M c64): the product of the
-// diagonal of L.  out[0] receives it, out[1] = 1 when a pivot was not
-// positive (or not a number).  One workgroup, a barrier per column.
+// sqrt(det(I - O)) of an M-mode O (device, leading dimension ld, 0: packed
+// lower triangle), M <= STAGE_LDS_MODES: the Hermitian completion of the lower
+// triangle of C = I - O, its rows reordered to mode pairs, is eliminated in
+// LDS one mode (2x2 pivot) at a time, from the last to the first.  A step
+// rewrites only blocks of the modes that remain, each by the thread that
+// reads it, so it needs one barrier; every thread forms the pivot itself.
+// out[0] receives the root of the product of the pivots' determinants, out[1]
+// = 1 when a pivot was not positive (or not a number).  What bounds it is the
+// chain of M such steps, about 0.3 us each.
+template <int NT>
+__global__ void __launch_bounds__(NT) tor_sqrt_det_lds(const double *O, long ld, int M, double *out)
+{
+    __shared__ c64 A[4][NB(STAGE_LDS_MODES)];  // entry e of block (a, b), a >= b, at [e][bidx(a, b)]
+    const int t = threadIdx.x;
+    const View v{O, ld, M, nullptr, M, nullptr};
+    for (int q = t; q < 4 * NB(M); q += NT) {
+        int a, b;
+        block_ab(q >> 2, a, b);
+        const int e = q & 3, ci = e >> 1, cj = e & 1;
+        A[e][q >> 2] = v.c(a + ci * M, b + cj * M);
+    }
+    __syncthreads();
+    double prod = 1.0;
+    bool bad = false;
+    for (int m = M - 1; m >= 0; --m) {
+        const int d = bidx(m, m);
+        const Piv<c64> pv = pivot<c64>(A[0][d].x, A[2][d], A[3][d].x);
+        if (!(A[0][d].x > 0.0) || !(pv.pdet > 0.0))
+            bad = true;
+        prod *= sqrt(pv.pdet);
+        for (int bi = t; bi < NB(m); bi += NT) {
+            int a, b;
+            block_ab(bi, a, b);
+            c64 x[4], y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[e] = A[e][bidx(m, a)];
+                y[e] = A[e][bidx(m, b)];
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                // rows of the LDL form of the pivot: r1, and r2 - r1 beta / alpha
+                x[2 + c] = sub_mul(x[2 + c], x[c], pv.ba);
+                y[2 + c] = sub_mul(y[2 + c], y[c], pv.ba);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int c = e >> 1, f = e & 1;
+                A[e][bi] = upd(A[e][bi], scale(x[c], pv.inv_a), y[f], scale(x[2 + c], pv.inv_g), y[2 + f]);
+            }
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        out[0] = prod;
+        out[1] = bad ? 1.0 : 0.0;
+    }
+}
+
+// the same for more modes, by a Cholesky factorisation in the caller's scratch
+// (2M x 2M c64): the product of the diagonal of L.  One workgroup, two
+// barriers per column.
 template <int NT>
 __global__ void __launch_bounds__(NT) tor_sqrt_det(const double *O, long ld, int M, c64 *A, double *out)
 {
@@ -367,6 +423,8 @@ __global__ void __launch_bounds__(NT) tor_sqrt_det(const double *O, long ld, int
 
 constexpr int STAGE_THREADS = 1024;
 constexpr int DET_THREADS = 1024;
+// 512 threads hold the blocks of 31 modes at one each
+constexpr int DET_LDS_THREADS = 512;
 
 hipError_t launch_stage(const StageDesc *descs, int count, hipStream_t s)
 {
@@ -376,14 +434,18 @@ hipError_t launch_stage(const StageDesc *descs, int count, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_stage_one(const StageDesc &d, StageInfo *host_info, unsigned long long *zero, int nzero, hipStream_t s)
+hipError_t launch_stage_one(const StageDesc &d, unsigned long long *zero, int nzero, hipStream_t s)
 {
-    hipLaunchKernelGGL((tor_stage_one<STAGE_THREADS>), dim3(1), dim3(STAGE_THREADS), 0, s, d, host_info, zero, nzero);
+    hipLaunchKernelGGL((tor_stage_one<STAGE_THREADS>), dim3(1), dim3(STAGE_THREADS), 0, s, d, zero, nzero);
     return hipGetLastError();
 }
 
 hipError_t launch_sqrt_det(const double *O, long ld, int M, c64 *scratch, double *out, hipStream_t s)
 {
+    if (M <= STAGE_LDS_MODES) {
+        hipLaunchKernelGGL((tor_sqrt_det_lds<DET_LDS_THREADS>), dim3(1), dim3(DET_LDS_THREADS), 0, s, O, ld, M, out);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((tor_sqrt_det<DET_THREADS>), dim3(1), dim3(DET_THREADS), 0, s, O, ld, M, scratch, out);
     return hipGetLastError();
 }
