@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <climits>
 #include <cmath>
 #include <condition_variable>
 #include <cstdio>
@@ -76,6 +77,7 @@ struct Request {
     double *dSlots = nullptr;
     float device_ms = 0.f;
     int launches = 0;       // serving launches that ran part of it
+    long long work_left() const { return (nroots - next_root) * root_work; }
     int flights = 0;            // serving launches in flight that hold some of its roots
     bool quick_flight = false;  // one of them is an express launch
     bool failed = false;        // a launch of it failed: retired with that status
@@ -1308,6 +1310,9 @@ size_t request_bytes(int n, unsigned sflags)
 // puts waves on every SIMD of its CU, so none may hold two express waves
 // (5 waves per CU let staging wait in 1-2 % of rounds, p99 0.47 ms).
 constexpr int SERVE_QUICK_CUS = 16;
+// Requests of at most this much work go to the express CUs beside a chunk
+// whatever is left of it (about 10 us of theirs at half their waves).
+constexpr long long SERVE_EXPRESS_ANY = 1ll << 17;
 // How long before the running chunk's expected end the next one is queued
 // behind it: the scheduler's polling interval and a launch's host time,
 // with room to spare.
@@ -1320,7 +1325,7 @@ struct ServeLaunch {
     int path = PATH_REAL;
     int slot = 0;                 // the lane slot of its buffers and events
     long long subsets = 0;        // its work
-    double end_est = 0.0;         // when it should end (steady-clock seconds; 0: unknown)
+    double end_est = 0.0;         // when it should end (steady-clock seconds)
     std::vector<Request *> used;  // one entry per root range (a request may hold two)
     std::vector<int> red;         // entries of used whose request the launch completes
 };
@@ -1375,20 +1380,23 @@ enum { TAKE_SMALL, TAKE_LARGE, TAKE_ANY };  // which requests a serving round ta
 // on lane's current stream and slot, with the tuned waves per CU of their
 // largest size (at most wpc_max when positive) on `cus` CUs; rec records
 // it.  TAKE_SMALL takes only the requests whose remaining work is at most
-// cfg.express_subsets, TAKE_LARGE only the others.  An express launch (quick
+// cfg.express_subsets, TAKE_LARGE only the others; none takes a request of
+// more than `most` subsets of work left.  An express launch (quick
 // set) leaves out every request with roots in flight; a chunked one only
 // those in an express launch, since chunks run one after another on their
 // lane's stream, so a request may hold roots in two queued chunks (and the
 // later one reduces it).  Called with ctx->mu held.
 int serve_round(tor_ctx *ctx, const ServeCfg &cfg, int path, std::vector<Request *> &active,
-                std::vector<Request *> &finished, int take_kind, long long budget, int cus, int wpc_max,
+                std::vector<Request *> &finished, int take_kind, long long budget, long long most, int cus, int wpc_max,
                 LaunchLane &lane, bool quick, ServeLaunch &rec)
 {
     std::vector<Request *> cand;
     for (Request *r : active) {
         if (r->path != path || r->failed || r->next_root >= r->nroots || r->quick_flight || (quick && r->flights > 0))
             continue;
-        const bool small = (r->nroots - r->next_root) * r->root_work <= cfg.express_subsets;
+        if (r->work_left() > most)
+            continue;
+        const bool small = r->work_left() <= cfg.express_subsets;
         if (take_kind == TAKE_ANY || small == (take_kind == TAKE_SMALL))
             cand.push_back(r);
     }
@@ -1397,7 +1405,7 @@ int serve_round(tor_ctx *ctx, const ServeCfg &cfg, int path, std::vector<Request
     Request *oldest = *std::min_element(cand.begin(), cand.end(),
                                         [](Request *a, Request *b) { return a->ticket < b->ticket; });
     std::stable_sort(cand.begin(), cand.end(), [](Request *a, Request *b) {
-        return (a->nroots - a->next_root) * a->root_work < (b->nroots - b->next_root) * b->root_work;
+        return a->work_left() < b->work_left();
     });
     std::vector<ProblemDesc> descs;
     std::vector<Request *> used;
@@ -1420,7 +1428,7 @@ int serve_round(tor_ctx *ctx, const ServeCfg &cfg, int path, std::vector<Request
     };
     // a small request is taken whole or not at all, so that it takes one
     // launch; a large one's share may end anywhere
-    auto left = [](const Request *r) { return (r->nroots - r->next_root) * r->root_work; };
+    auto left = [](const Request *r) { return r->work_left(); };
     auto small = [&](const Request *r) { return left(r) <= cfg.express_subsets; };
     take(oldest, small(oldest) ? left(oldest) : (long long)(cfg.oldest_share * (double)budget));
     for (Request *r : cand) {
@@ -1504,22 +1512,29 @@ bool poll_launch(const LaunchLane &lane, ServeLaunch &rec, std::vector<Request *
 // the chunk lane runs chunked launches of at most cfg.chunk_subsets on all
 // CUs but SERVE_QUICK_CUS of them; the quick lane runs express launches of
 // small requests, on those SERVE_QUICK_CUS CUs while a chunk is in flight
-// (half full, with about as much work as they do in a chunk's time), on the
+// (half full, with no more work than they do until it is due to end), on the
 // whole device otherwise.  Staging runs on those CUs too while a chunk is in
 // flight, on the context's stream otherwise.
 // Each round retires the launches that have ended, enqueues the next chunk,
 // stages the newly admitted requests, enqueues an express launch, and
 // publishes the finished requests; while launches are in flight it polls
 // their events.  A chunk takes the requests too large for express launches,
-// and small ones only while the express lane is busy.  So a small request
-// waits for neither the chunk in flight nor a large request: only for the
-// express launch before it.
+// and small ones only while the express lane is busy or one of them is too
+// large for what the express CUs do until the chunk ends.  So a small request
+// waits for no large one: only for the express launch before it, or for the
+// chunk in flight when that ends sooner than the express CUs would be done.
 void serve_loop(tor_ctx *ctx)
 {
     std::vector<Request *> active;
     std::deque<ServeLaunch> chunks;  // in flight on the chunk lane, in stream order (at most two)
     ServeLaunch quick;               // in flight on the express lane
-    double rate[NPATH] = {};         // kernel ms per subset of the recent chunks, per path
+    // kernel ms per subset of the recent chunks, per path (to begin with, what
+    // the kernels do on this part: 4.1e11, 1.1e11 and 4.7e10 subsets/s)
+    double rate[NPATH];
+    rate[PATH_REAL] = 2.4e-9;
+    rate[PATH_CPLX] = 9.1e-9;
+    rate[PATH_QUAD] = 2.1e-8;
+    bool deferred = false;  // a small request waits that the express CUs would keep longer than the chunk does
     int next_chunk = 0, next_quick = 0;  // each lane takes the paths in turn
     auto now_s = [] {
         return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
@@ -1614,15 +1629,15 @@ void serve_loop(tor_ctx *ctx)
             // while the host sees the end and launches the next.
             auto start_chunk = [&] {
                 if (chunks.size() >= 2 ||
-                    (chunks.size() == 1 && !(chunks.back().end_est > 0.0 && now_s() >= chunks.back().end_est - SERVE_QUEUE_LEAD_S)))
+                    (chunks.size() == 1 && now_s() < chunks.back().end_est - SERVE_QUEUE_LEAD_S))
                     return;
                 ServeLaunch rec;
                 for (int kind : {TAKE_LARGE, TAKE_ANY}) {
-                    if (kind == TAKE_ANY && cfg.express_subsets > 0 && !quick.busy)
-                        break;
+                    if (kind == TAKE_ANY ? cfg.express_subsets > 0 && !quick.busy && !deferred : deferred)
+                        continue;
                     for (int i = 0; i < NPATH && !rec.busy; i++) {
                         const int path = kPaths[(next_chunk + i) % NPATH];
-                        serve_round(ctx, cfg, path, active, finished, kind, cfg.chunk_subsets,
+                        serve_round(ctx, cfg, path, active, finished, kind, cfg.chunk_subsets, LLONG_MAX,
                                     ctx->chunk.cus > 0 ? ctx->chunk.cus : ctx->num_cu, 0, ctx->chunk, false, rec);
                         if (rec.busy)
                             next_chunk = (next_chunk + i + 1) % NPATH;
@@ -1633,9 +1648,8 @@ void serve_loop(tor_ctx *ctx)
                 if (!rec.busy)
                     return;
                 const double t = now_s();
-                const bool known = rate[rec.path] > 0.0 && (chunks.empty() || chunks.back().end_est > 0.0);
                 const double start = chunks.empty() ? t : std::max(t, chunks.back().end_est);
-                rec.end_est = known ? start + 1e-3 * rate[rec.path] * (double)rec.subsets : 0.0;
+                rec.end_est = start + 1e-3 * rate[rec.path] * (double)rec.subsets;
                 chunks.push_back(std::move(rec));
             };
             if (rc == TOR_OK)
@@ -1691,15 +1705,32 @@ void serve_loop(tor_ctx *ctx)
                 // lane's own CUs, with about the work those CUs do in a
                 // chunk's time, or on the whole device when no chunk runs
                 const bool chunk_busy = !chunks.empty();
+                deferred = false;
                 if (cfg.express_subsets > 0 && !quick.busy && (!chunk_busy || beside)) {
                     ctx->quick.cur = chunk_busy ? ctx->quick.stream : ctx->quick.wide;
                     const int cus = chunk_busy ? ctx->quick.cus : ctx->num_cu;
-                    const long long budget =
-                        chunk_busy ? std::max(1ll, cfg.chunk_subsets / ctx->num_cu * cus) : (1ll << 62);
                     for (int i = 0; i < NPATH && !quick.busy; i++) {
                         const int path = kPaths[(next_quick + i) % NPATH];
-                        serve_round(ctx, cfg, path, active, finished, TAKE_SMALL, budget, cus,
+                        // beside a chunk, no more than the express CUs do until
+                        // the chunk lane is due to be free (by the chunks'
+                        // rate): a launch that outlasts it would hold its
+                        // requests on 16 CUs while the others are idle (a burst
+                        // of 48 requests of 8 to 25 modes took 3.8 ms, 3.7 of
+                        // them one such launch beside a chunk of 0.2).  What
+                        // does not fit is left to the next chunk, or to the
+                        // whole device once the chunks have ended.
+                        long long budget = 1ll << 62;
+                        if (chunk_busy) {
+                            const double left_ms = 1e3 * std::max(0.0, chunks.back().end_est - now_s());
+                            budget = std::min((long long)(left_ms / rate[path] * cus / (ctx->num_cu - cus)),
+                                              cfg.chunk_subsets / ctx->num_cu * cus);
+                        }
+                        const long long most = std::max(budget, SERVE_EXPRESS_ANY);
+                        serve_round(ctx, cfg, path, active, finished, TAKE_SMALL, budget, most, cus,
                                     chunk_busy ? std::max(1, ctx->fit[path] / 2) : 0, ctx->quick, true, quick);
+                        for (Request *r : active)
+                            deferred |= chunk_busy && r->path == path && !r->failed && r->flights == 0 &&
+                                        r->next_root < r->nroots && r->work_left() <= cfg.express_subsets && r->work_left() > most;
                         if (quick.busy)
                             next_quick = (next_quick + i + 1) % NPATH;
                     }
