@@ -197,11 +197,15 @@ int main_store_occupancy();
 // exact double-double subset sums g[S] = sum over Z subset of S of t[Z], for
 // the 2^nbits terms t (tor_zeta.hip)
 hipError_t launch_zeta(const double *t, ddr *g, int nbits, hipStream_t s);
-// per click pattern S of M modes (bit i = API mode i) of a staged form of N
-// modes: Tor(O_S) = (-1)^(N-|S|) g[S reversed over N bits], and optionally
-// p(S) = Tor(O_S) sqrt(det(I - O)) (tor_zeta.hip)
-hipError_t launch_click_out(const ddr *g, int N, int M, const double *sqrt_det, double *probs, double *tor_hi,
-                            double *tor_lo, hipStream_t s);
+// the subset sums g of the 2^N terms t and, per click pattern S of M modes (bit
+// i = API mode i) of a staged form of N modes, Tor(O_S) = (-1)^(N-|S|) g[S
+// reversed over N bits] and p(S) = Tor(O_S) sqrt(det(I - O)), each output if
+// its pointer is not null; full receives the sum of the pattern of every mode.
+// g is workspace: the sums need not all be stored (tor_zeta.hip).  Null in a
+// host-only build of the runtime without the kernels.
+__attribute__((weak)) hipError_t launch_click_transform(const double *t, ddr *g, int N, int M, const double *sqrt_det,
+                                                        double *probs, double *tor_hi, double *tor_lo, ddr *full,
+                                                        hipStream_t s);
 hipError_t launch_reduce(const ProblemDesc *probs, int nprob, double *results, bool dd, hipStream_t s);
 hipError_t launch_zero(unsigned long long *p, int count, hipStream_t s);
 hipError_t launch_plain(const PlainParams &p, bool real, int grid, hipStream_t s);

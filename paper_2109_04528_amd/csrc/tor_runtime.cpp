@@ -2316,6 +2316,8 @@ int tor_click_all(tor_ctx *ctx, int M, const double *O, long ld, double *probs, 
     // the terms are stored by the FP64 kernel of the real quadrature form
     if (ctx->opt.flags & (TOR_FORCE_COMPLEX | TOR_FACTOR_DD))
         return TOR_E_INVAL;
+    if (!launch_click_transform)
+        return TOR_E_DEVICE;
     if (M == 0) {  // the empty pattern of a 0-mode state: Tor = 1, p = 1
         const double one[2] = {1.0, 0.0};
         if (dev_out && (probs || tor_hi)) {
@@ -2444,17 +2446,17 @@ int tor_click_all(tor_ctx *ctx, int M, const double *O, long ld, double *probs, 
         return TOR_E_NOT_PD;
     if (res[3] > 0.0)
         return TOR_E_NUMERIC;
-    e = hipEventRecord(ctx->ev0, ctx->stream);
-    if (e == hipSuccess)
-        e = launch_zeta(dTerms, dG, N, ctx->stream);
     // where the kernel writes: the caller's device arrays, pinned memory, or
     // the workspace (the latter two then copied to the caller's host arrays)
     double *stage = pinned_out ? (double *)(ctx->hout + 256) : (double *)(ctx->ws + oOut);
     double *pP = probs ? (dev_out ? probs : stage) : nullptr;
     double *pH = tor_hi ? (dev_out ? tor_hi : stage + (probs ? nP : 0)) : nullptr;
     double *pL = tor_lo ? (dev_out ? tor_lo : stage + (probs ? nP : 0) + nP) : nullptr;
-    if (e == hipSuccess && (pP || pH))
-        e = launch_click_out(dG, N, M, dDet, pP, pH, pL, ctx->stream);
+    // the whole state's Tor for out: the subset sum of the pattern of every
+    // mode, with the sign (-1)^(N-M) that turns a subset sum into a Torontonian
+    e = hipEventRecord(ctx->ev0, ctx->stream);
+    if (e == hipSuccess)
+        e = launch_click_transform(dTerms, dG, N, M, dDet, pP, pH, pL, hFull, ctx->stream);
     if (e == hipSuccess)
         e = hipEventRecord(ctx->ev1, ctx->stream);
     struct Out {
@@ -2465,11 +2467,6 @@ int tor_click_all(tor_ctx *ctx, int M, const double *O, long ld, double *probs, 
     for (const Out &o : outs)
         if (e == hipSuccess && o.to && !dev_out && !pinned_out)
             e = hipMemcpyAsync(o.to, o.from, sizeof(double) * nP, hipMemcpyDeviceToHost, ctx->stream);
-    // the whole state's Tor for out: the subset sum of the pattern of every
-    // mode (index bit N-1-q for mode q: the top M bits), with the sign
-    // (-1)^(N-M) that turns a subset sum into a Torontonian
-    if (e == hipSuccess && out)
-        e = hipMemcpyAsync(hFull, dG + ((nP - 1) << (N - M)), sizeof(ddr), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess)
         e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess)
