@@ -56,6 +56,15 @@ struct ProblemDesc {
 
 struct StageInfo;
 
+// What one evaluation gives back, in pinned memory: the last kernel of its
+// chain writes the verdict and then the flag.
+struct EvalResult {
+    double v[4];  // hi, lo, sum of |t|, flag of the slots
+    double ms;    // the recursive kernel's time
+    int status, path, N, unused;  // the staging kernel's verdict
+    unsigned long long done;      // the evaluation's number, once all else is there
+};
+
 struct MainParams {
     const ProblemDesc *probs;     // nprob descriptors; null: `one` is the only matrix
     int nprob;
@@ -70,7 +79,8 @@ struct MainParams {
                                   // signed term of each subset, indexed by subset
                                   // (bit N-1-l = decision at level l); else null
     const StageInfo *gate;        // run only if the staging kernel gave gate_path (null: always)
-    double *result;               // a launch of one root: its slot's values go here too (or null)
+    EvalResult *result;           // a launch of one root: its slot's values go here too (or null)
+    unsigned long long done;      // with result: the last kernel of its chain, which announces this number
     long long *clock;             // the device clock at the kernel's start goes here (or null)
     double ms_per_tick;           // of that clock
     int tickets_only;             // blocks may start late: no item is any block's own
@@ -222,7 +232,7 @@ constexpr int FMA_PROBE_CHAINS = 16;
 // matrix is staged already (st.info holds the verdict).
 struct EvalOne {
     bool stage;
-    StageDesc st;                  // st.info: device memory, st.info2: pinned
+    StageDesc st;                  // st.info: device memory
     unsigned long long *counters;  // device: a queue head per run
     int nrun;
     struct Run {
@@ -234,7 +244,8 @@ struct EvalOne {
     } run[2];
     bool dd;           // sum in double-double
     long long *clock;  // device: when the recursive kernel started
-    double *result;    // pinned: hi, lo, sum of |t|, flag, and the recursive kernel's time in ms
+    EvalResult *result;       // pinned
+    unsigned long long done;  // its number (not 0)
 };
 // null in a host-only build of the runtime without the kernels, which then
 // takes the general path

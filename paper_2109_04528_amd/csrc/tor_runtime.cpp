@@ -139,6 +139,7 @@ struct tor_ctx {
     size_t hstate_bytes = 0;
     char *hout = nullptr;    // what a click_all call reads back
     size_t hout_bytes = 0;
+    unsigned long long eval_no = 0;  // number of the last lone evaluation
     TuneEntry tune[NPATH][MAX_N + 1];
     std::string arch;
 
@@ -1037,6 +1038,9 @@ bool args_ok(const tor_ctx *ctx, int n, const double *O, long ld)
     return n >= 0 && n <= ctx->opt.max_n && (n == 0 || (O && ld >= 2L * n));
 }
 
+// How long a lone evaluation's end is looked for by the host itself.
+constexpr std::chrono::microseconds EVAL_SPIN(300);
+
 // One matrix without a host round trip between staging and the recursive
 // kernel: everything is enqueued at once, and the kernel of the path that the
 // staging kernel does not choose returns at once.  A host matrix's lower
@@ -1123,10 +1127,8 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
     }
     ev.st.info = (StageInfo *)ctx->ws;
     ev.st.out = ctx->ws + oForm;
-    StageInfo *info = (StageInfo *)ctx->hdown;
-    double *res = (double *)(ctx->hdown + 256);
+    EvalResult *res = (EvalResult *)ctx->hdown;
     ev.stage = true;
-    ev.st.info2 = info;
     ev.counters = (unsigned long long *)(ctx->ws + oCount);
     ev.nrun = np;
     ev.dd = ctx->opt.accum != TOR_ACCUM_FP64 || paths[0] == PATH_QUAD;
@@ -1140,19 +1142,41 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
         r.P.slots = (double *)(ctx->ws + oSlots);
         r.scratch = ctx->ws + off;
     }
+    // Enqueue the chain and wait for its end: for a short while by looking at
+    // the number its last kernel writes, then (a long evaluation, or an error
+    // that keeps it from being written) by the stream.
+    auto go = [&]() -> hipError_t {
+        ev.done = ++ctx->eval_no;
+        __atomic_store_n(&res->done, 0ull, __ATOMIC_RELAXED);
+        hipError_t err = launch_eval_one(ev, ctx->stream);
+        if (err != hipSuccess) {
+            (void)hipStreamSynchronize(ctx->stream);  // what was enqueued before the failure
+            return err;
+        }
+        const auto t0 = std::chrono::steady_clock::now();
+        for (;;) {
+            for (int i = 0; i < 64; i++)
+                if (__atomic_load_n(&res->done, __ATOMIC_ACQUIRE) == ev.done)
+                    return hipSuccess;
+            if (std::chrono::steady_clock::now() - t0 > EVAL_SPIN)
+                break;
+        }
+        err = hipStreamSynchronize(ctx->stream);
+        if (err == hipSuccess && __atomic_load_n(&res->done, __ATOMIC_ACQUIRE) != ev.done)
+            err = hipErrorInvalidValue;
+        return err;
+    };
     hipError_t e = hipSetDevice(ctx->device);
     if (e == hipSuccess)
-        e = launch_eval_one(ev, ctx->stream);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(ctx->stream);
+        e = go();
     if (e != hipSuccess)
         return hip_status(e);
     Mat m;
     m.n = n;
-    m.N = info->N;
-    m.path = info->path;
+    m.N = res->N;
+    m.path = res->path;
     m.ws_off = oForm;
-    if (info->status != 0) {
+    if (res->status != 0) {
         *out = tor_result{};
         out->status = TOR_E_INVAL;
         return TOR_E_INVAL;
@@ -1165,17 +1189,15 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
             return TOR_E_DEVICE;
         std::swap(ev.run[0], ev.run[1]);
         ev.stage = false;
-        e = launch_eval_one(ev, ctx->stream);
-        if (e == hipSuccess)
-            e = hipStreamSynchronize(ctx->stream);
+        e = go();
         if (e != hipSuccess)
             return hip_status(e);
         at = 0;
     }
     const EvalOne::Run &r = ev.run[at];
-    const float ms = (float)res[4];
+    const float ms = (float)res->ms;
     std::vector<int> runs(1, 1);
-    double v[4] = {res[0], res[1], res[2], res[3]};
+    double v[4] = {res->v[0], res->v[1], res->v[2], res->v[3]};
     if (v[3] == SLOT_NUMERIC) {
         std::vector<double> rv(v, v + 4);
         rc = rerun_failed(ctx, m.path, std::vector<ProblemDesc>(1, r.P), rv, std::vector<size_t>(1, oSlots), r.P.nroots, off,

@@ -145,26 +145,42 @@ __device__ inline hd quad_entry(const View &v, int mi, int mj, int ci, int cj)
 
 __device__ inline double sq(double x, double y) { return x * x + y * y; }
 
-// block-wide maxima of the K values v (every thread receives them); red
-// holds K * NT / 64 doubles
-template <int NT, int K>
-__device__ inline void block_max(double (&v)[K], double *red)
+// v with the lane's neighbour under a DPP pattern (lanes without one get 0)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v)
 {
-    const int t = threadIdx.x;
-    for (int k = 0; k < K; ++k)
-        for (int off = 32; off >= 1; off >>= 1)
-            v[k] = fmax(v[k], __shfl_xor(v[k], off));
-    __syncthreads();
-    if ((t & 63) == 0)
-        for (int k = 0; k < K; ++k)
-            red[k * (NT / 64) + (t >> 6)] = v[k];
-    __syncthreads();
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Block-wide maxima of the K non-negative values v (infinity included; no
+// NaN): every thread receives them.  best[K] is zero, and a barrier has passed
+// since.  Within a wave by DPP moves on the vector unit, then one LDS atomic
+// per wave on the bit patterns, whose order is that of non-negative doubles:
+// lane shuffles and a read of every wave's maximum went through LDS 960 times
+// per workgroup, which took longer than all else the kernel does.
+template <int K>
+__device__ __forceinline__ void block_max(double (&v)[K], unsigned long long *best)
+{
+#pragma unroll
     for (int k = 0; k < K; ++k) {
-        double r = red[k * (NT / 64)];
-        for (int w = 1; w < NT / 64; ++w)
-            r = fmax(r, red[k * (NT / 64) + w]);
-        v[k] = r;
+        v[k] = fmax(v[k], dpp_or_zero<0x111, 0xf>(v[k]));  // row_shr:1
+        v[k] = fmax(v[k], dpp_or_zero<0x112, 0xf>(v[k]));  // row_shr:2
+        v[k] = fmax(v[k], dpp_or_zero<0x114, 0xf>(v[k]));  // row_shr:4
+        v[k] = fmax(v[k], dpp_or_zero<0x118, 0xf>(v[k]));  // row_shr:8
+        v[k] = fmax(v[k], dpp_or_zero<0x142, 0xa>(v[k]));  // row_bcast:15
+        v[k] = fmax(v[k], dpp_or_zero<0x143, 0xc>(v[k]));  // row_bcast:31
     }
+    if ((threadIdx.x & 63) == 63)
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            atomicMax(&best[k], __builtin_bit_cast(unsigned long long, v[k]));
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        v[k] = __builtin_bit_cast(double, best[k]);
 }
 
 }  // namespace
@@ -179,9 +195,11 @@ constexpr int STAGE_LDS_ENTRIES = NB(2 * STAGE_LDS_MODES);
 template <int NT>
 __device__ __forceinline__ void stage_matrix(const StageDesc &D)
 {
-    __shared__ double red[5 * (NT / 64)];
+    __shared__ unsigned long long best[5];
     __shared__ c64 tri[STAGE_LDS_ENTRIES];
     const int t = threadIdx.x;
+    if (t < 5)
+        best[t] = 0ull;
     const int n = D.n, n2 = 2 * n;
     const bool in_lds = NB(n2) <= STAGE_LDS_ENTRIES;
     View v{D.O, D.ld, n, D.sel, D.M, nullptr};
@@ -236,13 +254,16 @@ __device__ __forceinline__ void stage_matrix(const StageDesc &D)
             dev2 = fmax(dev2, sq(d2a.x - d2b.x, d2a.y - d2b.y));
         }
     }
-    double mx[5] = {nonfin, cmax2, dev2, hs2, hd2};
-    block_max<NT, 5>(mx, red);
+    double mx[3] = {nonfin, cmax2, dev2}, mh[2] = {hs2, hd2};
+    block_max(mx, best);
     nonfin = mx[0];
     cmax2 = mx[1];
     dev2 = mx[2];
-    hs2 = mx[3];
-    hd2 = mx[4];
+    if (herm) {
+        block_max(mh, best + 3);
+        hs2 = mh[0];
+        hd2 = mh[1];
+    }
     const double tol = 64.0 * kStageU * fmax(sqrt(cmax2), 1.0);
     const bool structured = want_real && dev2 <= tol * tol;
     int status = 0;
@@ -436,7 +457,12 @@ hipError_t launch_stage(const StageDesc *descs, int count, hipStream_t s)
 
 hipError_t launch_stage_one(const StageDesc &d, unsigned long long *zero, int nzero, hipStream_t s)
 {
-    hipLaunchKernelGGL((tor_stage_one<STAGE_THREADS>), dim3(1), dim3(STAGE_THREADS), 0, s, d, zero, nzero);
+    // a thread per entry of the lower triangle: fewer waves meet at fewer
+    // barriers (n = 10: 5.7 us against 6.1)
+    if (d.n <= 11)
+        hipLaunchKernelGGL((tor_stage_one<256>), dim3(1), dim3(256), 0, s, d, zero, nzero);
+    else
+        hipLaunchKernelGGL((tor_stage_one<STAGE_THREADS>), dim3(1), dim3(STAGE_THREADS), 0, s, d, zero, nzero);
     return hipGetLastError();
 }
 
