@@ -365,9 +365,9 @@ __device__ void elim_inplace(const S *src, int snb, S *dst, int dnb, int s, int 
     elim_global_body(src, snb, dst, dnb, (S *)nullptr, 0, s, lane, pdet, bad);
 }
 
-// the root path in LDS: one include step in place on a node of s modes with
-// nb blocks per granule array (each lane rewrites only blocks it reads, and
-// never a pivot row, as in elim_inplace)
+// one include step in place in LDS on a node of s modes with nb blocks per
+// granule array (each lane rewrites only blocks it reads, and never a pivot
+// row, as in elim_inplace)
 template <class S>
 __device__ __forceinline__ void elim_lds(S *node, int nb, int s, int lane, RT<S> &pdet, int &bad)
 {
@@ -459,65 +459,72 @@ __device__ __forceinline__ void restride_node(S *node, int nb, int s, int lane)
 }
 
 // ---------------------------------------------------------------------------
-// View t of the tier-B tables: for the node of level jl with id i (bit
-// jl-1-m of i = decision on the m-th mode below the tier-A leaf, 1 =
-// include; t = (2^jl - 1) + i) the LDS offset of the stored node it is a
-// view of, that node's blocks per granule array, and the slot of its
-// determinant (0xff: the tier-A leaf).  The include node (lev, idx) keeps
-// its determinant at (2^(lev-1) - 1) + idx.
+// The tier-B tables, made at compile time and copied to LDS once per wave.
+// View t: for the node of level jl with id i (bit jl-1-m of i = decision on the
+// m-th mode below the tier-A leaf, 1 = include; t = (2^jl - 1) + i) the LDS
+// offset of the stored node it is a view of, that node's blocks per granule
+// array, and the slot of its determinant (0xff: the tier-A leaf).  The include
+// node (lev, idx) keeps its determinant at (2^(lev-1) - 1) + idx.  Per include
+// node i of level J (record (2^(J-1) - 1) + i, J = 1..B-1) its parent's stored
+// offset and blocks per array and its own stored offset, packed in 64 bits;
+// per block bi of a child (a, b) and its block index bidx(a, b) packed.
 template <int R, int B, int ESZ, int L, int X0>
-__device__ __forceinline__ void view_entry(int t, int &off, int &nb, int &det)
-{
-    static constexpr NodePlacement<R, B - 1, ESZ, L, X0> place{};
-    const int jl = 31 - __clz(t + 1);
-    const int i = t + 1 - (1 << jl);
-    if (i == 0) {
-        off = 0;
-        nb = NB(R + X0);
-        det = 0xff;
-    } else {
-        const int tz = __builtin_ctz(i);
-        const int lev = jl - tz;
-        const int idx = (i >> tz) >> 1;
-        off = place.off[(1 << (lev - 1)) + idx] / ESZ;
-        nb = NB(R - lev);
-        det = (1 << (lev - 1)) - 1 + idx;
+struct TierBTables {
+    static constexpr int NV = (1 << B) - 1, NR = (1 << (B - 1)) - 1, NK = NB(R - 1);
+    unsigned long long nodeRec[NR];
+    uint32_t blkRec[NK];
+    uint16_t srcOff[NV];
+    uint8_t srcNB[NV], srcDet[NV];
+    constexpr TierBTables() : nodeRec{}, blkRec{}, srcOff{}, srcNB{}, srcDet{}
+    {
+        constexpr NodePlacement<R, B - 1, ESZ, L, X0> place{};
+        for (int t = 0; t < NV; ++t) {
+            int jl = 0;
+            while ((2 << jl) <= t + 1)
+                ++jl;
+            const int i = t + 1 - (1 << jl);
+            int off = 0, nb = NB(R + X0), det = 0xff;
+            if (i != 0) {
+                int tz = 0;
+                while (((i >> tz) & 1) == 0)
+                    ++tz;
+                const int lev = jl - tz, idx = (i >> tz) >> 1;
+                off = place.off[(1 << (lev - 1)) + idx] / ESZ;
+                nb = NB(R - lev);
+                det = (1 << (lev - 1)) - 1 + idx;
+            }
+            srcOff[t] = (uint16_t)off;
+            srcNB[t] = (uint8_t)nb;
+            srcDet[t] = (uint8_t)det;
+        }
+        for (int J = 1; J < B; ++J)
+            for (int i = 0; i < 1 << (J - 1); ++i) {
+                const int t = (1 << (J - 1)) - 1 + i, c = (1 << J) - 1 + 2 * i + 1;
+                nodeRec[t] = (unsigned long long)(srcOff[t] * ESZ) | ((unsigned long long)(16 * srcNB[t]) << 16) |
+                             ((unsigned long long)(srcOff[c] * ESZ) << 32);
+            }
+        for (int a = 0, bi = 0; a < R - 1; ++a)
+            for (int b = 0; b <= a; ++b, ++bi)
+                blkRec[bi] = (uint32_t)(16 * bidx(a, b) | (16 * a) << 16 | (16 * b) << 24);
     }
-}
-
-// tier B tables, built once per wave: the view entries above; per include
-// node i of level J (record (2^(J-1) - 1) + i) its parent's stored offset
-// and blocks per array and its own stored offset, packed in 64 bits; per
-// block bi of a child (a, b) and its block index bidx(a, b) packed.
+};
 template <class S, int R, int B, int L>
 __device__ __forceinline__ void build_tables(uint16_t *srcOff, uint8_t *srcNB, uint8_t *srcDet,
                                              unsigned long long *nodeRec, uint32_t *blkRec, int lane)
 {
-    constexpr int esz = (int)sizeof(S);
     constexpr int X0 = std::is_same<S, double>::value ? 1 : 0;
-    for (int t = lane; t < (1 << B) - 1; t += 64) {
-        int off, nb, det;
-        view_entry<R, B, esz, L, X0>(t, off, nb, det);
-        srcOff[t] = (uint16_t)off;
-        srcNB[t] = (uint8_t)nb;
-        srcDet[t] = (uint8_t)det;
+    using Tab = TierBTables<R, B, (int)sizeof(S), L, X0>;
+    static constexpr Tab tab{};
+    static_assert(Tab::NV <= 64 && Tab::NK <= 64, "one entry per lane");
+    if (lane < Tab::NV) {
+        srcOff[lane] = tab.srcOff[lane];
+        srcNB[lane] = tab.srcNB[lane];
+        srcDet[lane] = tab.srcDet[lane];
     }
-    // include nodes of levels 1..B-1 (their children are views of level B-1
-    // at most)
-    for (int t = lane; t < (1 << (B - 1)) - 1; t += 64) {
-        const int J = 32 - __clz(t + 1);  // t = (2^(J-1) - 1) + i
-        const int i = t + 1 - (1 << (J - 1));
-        int poff, pnb, pdet, coff, cnb, cdet;
-        view_entry<R, B, esz, L, X0>(t, poff, pnb, pdet);
-        view_entry<R, B, esz, L, X0>((1 << J) + 2 * i, coff, cnb, cdet);
-        nodeRec[t] = (unsigned long long)(poff * esz) | ((unsigned long long)(16 * pnb) << 16) |
-                     ((unsigned long long)(coff * esz) << 32);
-    }
-    for (int bi = lane; bi < NB(R - 1); bi += 64) {
-        int a, b;
-        block_ab(bi, a, b);
-        blkRec[bi] = (uint32_t)(16 * bidx(a, b) | (16 * a) << 16 | (16 * b) << 24);
-    }
+    if (lane < Tab::NR)
+        nodeRec[lane] = tab.nodeRec[lane];
+    if (lane < Tab::NK)
+        blkRec[lane] = tab.blkRec[lane];
 }
 
 // LDS tables of tier B (see build_tables) and its per-node pivot scalars
