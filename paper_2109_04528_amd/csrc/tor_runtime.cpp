@@ -967,12 +967,30 @@ void fill_result(const Mat &st, int path, const double *r, float ms, tor_result 
     out->launches = 1;
 }
 
-// Split depths for a launch of several matrices: roots of about equal work,
-// about eight per persistent wave over the whole launch (a lone matrix keeps
-// its own tuned or default depth).  With four, the waves that draw the last
-// roots still run one when the others have none left; eight such roots
-// shorten that end by about as much as their extra root set-ups cost, and
-// sixteen or thirty-two gain nothing more.
+// Subsets per root (as a power of two) for a launch of several matrices with
+// 2^x subsets per persistent wave.  Large roots leave waves idle at the end,
+// small ones pay their set-up (up to N eliminations, about a leaf's time)
+// too often: a root of one leaf spends half its time on it.  So a wave's
+// share up to a few leaves is one root; beyond that one to three roots per
+// wave, and no root above the size whose set-up no longer shows.  Kernel
+// times (us) over every size from a sweep of 15 mixes per path, the rule's in
+// brackets: real x = 12.3 (n = 18) 63 [12] against 79 at eight roots per
+// wave, as before; x = 13.3 [13] 83 against 142; x = 14.0 [14] 105 against
+// 214; x = 15.2 (n = 27) [14] 228 against 291; x = 16.3 (256 of n = 8..22) [15]
+// 425 against 469; x = 21.2 (512 of n = 12..26) [16] 11 711 against 12 598.
+// Complex x = 11.5 [11] 78 against 160, x = 16.5 [14] 1414 against 1602;
+// double-double x = 12.2 [13] 238 against 348, x = 17.9 [13] 9712 against 9867.
+int batch_root_lg(int path, double x)
+{
+    if (path == PATH_REAL)
+        return x <= 15.1 ? std::min(14, (int)std::floor(x + 0.6)) : std::min(16, (int)std::floor(x - 1.1));
+    if (x < 12.0)
+        return std::min(11, (int)std::floor(x + (path == PATH_QUAD ? 0.4 : 0.6)));
+    return path == PATH_CPLX && x >= 16.3 ? 14 : 13;
+}
+
+// Split depths for a launch of several matrices: roots of about equal work
+// (a lone matrix keeps its own tuned or default depth).
 void batch_ks(const tor_ctx *ctx, int path, const std::vector<Mat *> &grp, std::vector<int> &ks)
 {
     if (grp.size() == 1 || ctx->opt.split_k > 0) {
@@ -986,8 +1004,7 @@ void batch_ks(const tor_ctx *ctx, int path, const std::vector<Mat *> &grp, std::
         work += std::ldexp(1.0, m->N);
         Nmax = std::max(Nmax, m->N);
     }
-    const double per_root = std::max(work / (8.0 * launch_grid(ctx, path, Nmax)), 1.0);
-    const int lg = (int)std::floor(std::log2(per_root) + 0.5);
+    const int lg = batch_root_lg(path, std::log2(work / launch_grid(ctx, path, Nmax)));
     for (size_t j = 0; j < grp.size(); j++) {
         const int N = grp[j]->N;
         ks[j] = std::max(0, std::min(N - lg, N - path_R(path)));
@@ -1303,7 +1320,10 @@ int serve_k(const tor_ctx *ctx, const ServeCfg &cfg, const Request &r)
     const int LA = std::max(r.N - path_R(r.path), 0);
     const double per_root = std::max((double)cfg.chunk_subsets / (4.0 * launch_grid(ctx, r.path, r.N)), 1.0);
     const int lg = (int)std::floor(std::log2(per_root));
-    const int k = std::max(choose_k(ctx, r.N, r.path), r.N - lg);
+    // and of two leaves at least: a request seldom has the device to itself, and
+    // a root of one leaf spends half its time on its set-up (bursts of 48 and
+    // 60 requests 812 and 1763 us with such roots, 756 and 1560 without)
+    const int k = std::max(std::min(choose_k(ctx, r.N, r.path), LA - 1), r.N - lg);
     return std::max(0, std::min(k, std::min(LA, 20)));
 }
 

@@ -50,3 +50,21 @@ def test_single_root_matrices_in_one_launch():
         for i in range(0, 300, 23):
             assert bits(got[i]) == bits(ref.eval(mats[i]))
         assert np.all([r.status == 0 for r in got])
+
+
+# subsets per wave from 2^1 to 2^15: roots of one leaf, of a few, several per wave
+@pytest.mark.parametrize("form", ["real", "hermitian", "dd"])
+@pytest.mark.parametrize("sizes", [(11, 3), (14, 15, 16), (18,) * 12, (20, 17, 12, 9, 19), (21, 22, 16), (23, 10, 22)])
+def test_batch_split_does_not_change_values(form, sizes):
+    from paper_2109_04528_amd import Context, TOR_FACTOR_DD
+    make = gen.random_hpd_O if form == "hermitian" else gen.random_O
+    mats = [make(n, 500 + 7 * i + n) for i, n in enumerate(sizes)]
+    say(f"case batch split {form} {sizes}")
+    with Context(flags=TOR_FACTOR_DD if form == "dd" else 0) as ctx:
+        for O, r in zip(mats, ctx.eval_batch(mats)):
+            lone = ctx.eval(O)
+            assert r.status == 0 and r.path == lone.path
+            if form == "real":  # exact sums of the same terms
+                assert (r.tor, r.tor_lo) == (lone.tor, lone.tor_lo)
+            else:  # the same terms, double-double sums of another grouping
+                assert abs((r.tor - lone.tor) + (r.tor_lo - lone.tor_lo)) <= 2.0 ** -90 * lone.sum_abs
