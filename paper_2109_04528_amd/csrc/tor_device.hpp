@@ -304,7 +304,8 @@ __device__ __forceinline__ Piv<ddr> pivot(ddr a, ddr b, ddr g)
 // exponent(r1) >= exponent(r0), or the difference is exact by Sterbenz's
 // lemma), i.e. whenever that mode's pivot determinant is at most 4.
 struct AccDD {
-    static constexpr bool kDD = true;  // reduce as double-double
+    static constexpr bool kDD = true;      // reduce as double-double
+    static constexpr bool kAnchored = false;
     double hi = 0.0, lo = 0.0, abs_sum = 0.0, frame = 1.0;
     __device__ __forceinline__ void begin_leaf(double *) {}
     __device__ __forceinline__ void two_sum(double t)
@@ -339,10 +340,108 @@ struct AccDD {
         frame = f;
     }
 };
+// The same double-double sum with fewer operations per term (the real path,
+// whose lanes add 32 terms per leaf).  Within a leaf the terms of either sign
+// are summed apart, each in a double that starts at an anchor A, a power of
+// two above all of them: then Dekker's Fast2Sum is exact for every addition
+// (3 operations, where TwoSum takes 6 and the pair's difference 3 more), and
+// the sum of |t| comes out of the two sums for nothing.  That is 8 operations
+// per pair of terms instead of 13.
+//
+// Every term is positive, so each sum only grows from A; if it ends below 2A,
+// every term was below A and every addition exact.  close() tests that; if it
+// fails in any lane, the leaf runs again with AccDD, and the anchor is put
+// higher for the leaves that follow.  Nothing is assumed of the matrix.
+//
+// The anchor is one for the wave, 2^lift times the first lane's first term
+// (the term of that lane's node alone, the smallest of the leaf for a Gaussian
+// state) to within a factor of 2.  The rounding errors that are summed in Pl
+// and Ml are multiples of the unit of the smallest term, at most 2^(lift - 53)
+// of it each, so sums of 16 stay exact up to lift = 50.  P - M is exact: both
+// are multiples of the unit of A and below 2A.
+// 2^lift times the power of two at det^(-1/2) of the first lane
+__device__ __forceinline__ double anchor_above(double det, int lift)
+{
+    const unsigned h = __builtin_amdgcn_readfirstlane((unsigned)(__builtin_bit_cast(unsigned long long, det) >> 32));
+    const int e = (int)((h >> 20) & 0x7ffu) - 1023;
+    const unsigned a = (unsigned)(1023 - (e >> 1) + lift) << 20;
+    return __builtin_bit_cast(double, (unsigned long long)a << 32);
+}
+// n = s + t, s >= t: the sum goes on in s, its rounding error in l
+__device__ __forceinline__ void anchored_add(double &s, double &l, double t)
+{
+    const double n = s + t;
+    l += t - (n - s);
+    s = n;
+}
+struct AccAnchor {
+    static constexpr bool kDD = true;
+    static constexpr bool kAnchored = true;
+    static constexpr int LIFT0 = 34, LIFT_MAX = 49;
+    double hi = 0.0, lo = 0.0, abs_sum = 0.0;
+    double P, Pl, M, Ml;
+    int lift = LIFT0;  // wave-uniform
+    static constexpr double frame = 1.0;
+    __device__ __forceinline__ void begin_leaf(double *) {}
+    __device__ __forceinline__ void set_frame(double) {}
+    __device__ __forceinline__ double anchor(double det) const { return anchor_above(det, lift); }
+    __device__ __forceinline__ void open(double a)
+    {
+        P = a;
+        M = a;
+        Pl = 0.0;
+        Ml = 0.0;
+    }
+    template <int SG>
+    __device__ __forceinline__ void one(double t)
+    {
+        if (SG > 0)
+            anchored_add(P, Pl, t);
+        else
+            anchored_add(M, Ml, t);
+    }
+    template <int SG, int TB = 0>
+    __device__ __forceinline__ void add(double r)
+    {
+        one<SG>(r);
+    }
+    template <int SG, int TB = 0>
+    __device__ __forceinline__ void add_pair(double r0, double r1)
+    {
+        one<-SG>(r0);
+        one<SG>(r1);
+    }
+    // hi + lo += s (th + tl), s = +-1
+    __device__ __forceinline__ void fold(double s, double th, double tl, double ab)
+    {
+        const double t = s * th;
+        const double n = hi + t;
+        const double bb = n - hi;
+        lo += (hi - (n - bb)) + (t - bb);
+        hi = n;
+        lo += s * tl;
+        abs_sum += ab;
+    }
+    // the leaf's sums, with the lane's sign s; false (in every lane) if the
+    // anchor was too low in any
+    __device__ __forceinline__ bool close(double s, double a)
+    {
+        // the empty asm keeps the rounding errors with their additions: left to
+        // the success branch, they hold every term and every partial sum
+        __asm__ volatile("" : "+v"(Pl), "+v"(Ml));
+        if (!__all(P < 2.0 * a && M < 2.0 * a && lift <= LIFT_MAX)) {
+            lift = min(lift + 5, LIFT_MAX + 1);
+            return false;
+        }
+        fold(s, P - M, Pl - Ml, ((P - a) + (M - a)) + (Pl + Ml));
+        return true;
+    }
+};
 // plain FP64 sum of the same terms, one by one, kept only for the dd-vs-FP64
 // comparison
 struct AccF64 {
     static constexpr bool kDD = false;
+    static constexpr bool kAnchored = false;
     double hi = 0.0, lo = 0.0, abs_sum = 0.0, frame = 1.0;
     __device__ __forceinline__ void begin_leaf(double *) {}
     template <int SG, int TB = 0>
@@ -368,18 +467,34 @@ struct AccF64 {
 // every term stored instead of summed (all click patterns at once): the lane's
 // 2^T terms of one tier-A leaf go to out[TB], TB the subset below the lane's
 // node (bit M-1 of TB = the decision when M modes are left), each with its
-// full sign (-1)^(#excluded); only the sum of |t| is kept
+// full sign (-1)^(#excluded).  The sum of |t| is kept as AccAnchor's is, leaf
+// by leaf the rounded exact sum, so that it is the same number bit for bit; a
+// term above the anchor costs it no more than an ordinary sum's rounding, so
+// nothing is tested.
 struct AccStore {
     static constexpr bool kDD = false;
+    static constexpr bool kAnchored = true;
     static constexpr double hi = 0.0, lo = 0.0;
     double abs_sum = 0.0, frame = 1.0;
+    double P, Pl;
     double *out = nullptr;
     __device__ __forceinline__ void begin_leaf(double *p) { out = p; }
+    __device__ __forceinline__ double anchor(double det) const { return anchor_above(det, AccAnchor::LIFT0); }
+    __device__ __forceinline__ void open(double a)
+    {
+        P = a;
+        Pl = 0.0;
+    }
+    __device__ __forceinline__ bool close(double, double a)
+    {
+        abs_sum += (P - a) + Pl;
+        return true;
+    }
     template <int SG, int TB = 0>
     __device__ __forceinline__ void add(double r)
     {
         *(__attribute__((address_space(1))) double *)(out + TB) = SG * frame * r;
-        abs_sum += r;
+        anchored_add(P, Pl, r);
     }
     template <int SG, int TB = 0>
     __device__ __forceinline__ void add_pair(double r0, double r1)
@@ -388,7 +503,8 @@ struct AccStore {
         typedef double v2 __attribute__((ext_vector_type(2)));
         const v2 v = {-SG * frame * r0, SG * frame * r1};
         *(__attribute__((address_space(1))) v2 *)(out + TB) = v;
-        abs_sum += r0 + r1;
+        anchored_add(P, Pl, r0);
+        anchored_add(P, Pl, r1);
     }
     __device__ __forceinline__ void set_frame(double f) { frame = f; }
 };
@@ -397,6 +513,7 @@ struct AccStore {
 // pair of the last mode is formed as a double-double difference first
 struct AccQ {
     static constexpr bool kDD = true;
+    static constexpr bool kAnchored = false;
     double hi = 0.0, lo = 0.0, abs_sum = 0.0, frame = 1.0;
     __device__ __forceinline__ void begin_leaf(double *) {}
     __device__ __forceinline__ void acc(double th, double tl)

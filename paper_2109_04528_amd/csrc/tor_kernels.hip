@@ -281,6 +281,7 @@ template <class S>
 __device__ __forceinline__ void elim_global_body(const S *src, int snb, S *dst, int dnb, S *lds, int nlds, int s,
                                                  int lane, RT<S> &pdet, int &bad)
 {
+    __asm__ volatile("" : "+v"(lane));  // as in copy_node
     const int m = s - 1;
     const Piv<S> pv = node_pivot_g(src, snb, m);
     pdet = pv.pdet;
@@ -315,7 +316,13 @@ __device__ void elim_global(const S *__restrict__ src, int snb, S *__restrict__ 
         elim_global_body(src, snb, dst, dnb, lds, nlds, s, lane, pdet, bad);
         return;
     }
-    const int bi0 = lane, bi1 = lane + 64;
+    // real path: the second block's coordinates are found again at every step
+    // (a step that makes a leaf has two lanes with one), which frees the
+    // registers that its accumulators take
+    int lane1 = lane;
+    if constexpr (std::is_same<S, double>::value)
+        __asm__ volatile("" : "+v"(lane1));
+    const int bi0 = lane, bi1 = lane1 + 64;
     const bool h0 = bi0 < nbo, h1 = bi1 < nbo;
     int a0 = 0, b0 = 0, a1 = 0, b1 = 0;
     block_ab(bi0, a0, b0);
@@ -415,6 +422,9 @@ __device__ __forceinline__ void copy_node(const S *src, int snb, S *dst, int dnb
 {
     constexpr int GPB = 4 / EPG((int)sizeof(S));  // granule arrays
     constexpr int U = GPB == 2 ? 4 : 1;
+    // the empty asm keeps what a lane derives from its index alone, the same in
+    // every call, from being held in registers through the whole kernel
+    __asm__ volatile("" : "+v"(lane));
     const int nb = NB(s);
     for (int b0 = lane; b0 < nb; b0 += 64 * U) {
         dv2 v[U][GPB];
@@ -441,6 +451,7 @@ template <class S, int SM>
 __device__ __forceinline__ void restride_node(S *node, int nb, int s, int lane)
 {
     constexpr int GPB = 4 / EPG((int)sizeof(S)), IT = (NB(SM) + 63) / 64;
+    __asm__ volatile("" : "+v"(lane));  // as in copy_node
     const int n = NB(s);
     dv2 v[IT][GPB];
 #pragma unroll
@@ -614,12 +625,13 @@ __device__ __forceinline__ void tierB_level(const TierB<S> &tb, RT<S> leafDet, i
     };
     constexpr int TOT = NN * NS, FULL = TOT / 64;
     // real path: an empty asm hides that the lane index is the same in every
-    // leaf, so the passes' node and block indices are recomputed per leaf
-    // instead of being held in registers across the whole leaf loop (10
-    // registers less, which the one-wait tier-A step uses; the complex path
-    // has them to spare)
+    // leaf, so the node and block indices of the passes of levels 3 and 4 are
+    // recomputed per leaf instead of being held in registers across the whole
+    // leaf loop (levels 1 and 2 fit: 249 registers; with the others the
+    // kernel passes 256 and half the waves go).  The 16-byte paths have
+    // registers to spare.
     int ln = lane;
-    if constexpr (std::is_same<S, double>::value)
+    if constexpr (std::is_same<S, double>::value && J > 2)
         __asm__ volatile("" : "+v"(ln));
 #pragma unroll 2
     for (int it0 = 0; it0 < 64 * FULL; it0 += 64)
@@ -753,8 +765,8 @@ __device__ __forceinline__ Piv<S> lane_pivot(RT<S> a, S b, RT<S> g, bool inc, in
 // once and receives the L rank-2 updates in turn, so only the pivot rows and
 // the T-mode result are held in registers.
 template <class S, int T, int B, int L, class Acc>
-__device__ __forceinline__ void tierC(const TierB<S> &tb, RT<S> leafDet, int leafInc, int N, int lane, Acc &acc,
-                                      int &bad, bool full_leaf)
+__device__ __forceinline__ void tierC_terms(const TierB<S> &tb, RT<S> leafDet, int leafInc, int N, int lane, Acc &acc,
+                                            int &bad, bool full_leaf, double &sign, double &anchor)
 {
     static_assert(L == 1 || L == 2, "one or two lane levels");
     constexpr int NP = (1 << (B - L)) - 1;  // table base of level B-L
@@ -826,10 +838,35 @@ __device__ __forceinline__ void tierC(const TierB<S> &tb, RT<S> leafDet, int lea
         }
     }
     const int excluded = (N - T) - includes;
-    acc.set_frame((excluded & 1) ? -1.0 : 1.0);
+    sign = (excluded & 1) ? -1.0 : 1.0;
+    acc.set_frame(sign);
+    if constexpr (Acc::kAnchored) {
+        anchor = acc.anchor(det);
+        acc.open(anchor);
+    }
     if (full_leaf)  // wave-uniform: the leaf that holds the all-include subset
         include_chain_test<S, T>(hT, bad);
     tail<S, T, 1, Acc>(hT, det, acc, bad);
+}
+
+template <class S, int T, int B, int L, class Acc>
+__device__ __forceinline__ void tierC(const TierB<S> &tb, RT<S> leafDet, int leafInc, int N, int lane, Acc &acc,
+                                      int &bad, bool full_leaf)
+{
+    double sign, anchor;
+    tierC_terms<S, T, B, L, Acc>(tb, leafDet, leafInc, N, lane, acc, bad, full_leaf, sign, anchor);
+    if constexpr (Acc::kAnchored) {
+        if (!acc.close(sign, anchor)) {
+            // once more from the LDS nodes, which are as they were (the empty
+            // asm: nothing of the first run is kept for this one)
+            __asm__ volatile("" : "+v"(lane));
+            if constexpr (Acc::kDD) {
+                AccDD leaf;
+                tierC_terms<S, T, B, L, AccDD>(tb, leafDet, leafInc, N, lane, leaf, bad, full_leaf, sign, anchor);
+                acc.fold(sign, leaf.hi, leaf.lo, leaf.abs_sum);
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1211,7 +1248,7 @@ hipError_t launch_main(int path, bool dd, const MainParams &p, int grid, hipStre
         return launch_main_quad(p, grid, s);
     } else if (path == PATH_REAL) {
         if (dd)
-            hipLaunchKernelGGL((tor_main<double, REAL_T, REAL_B, REAL_L, AccDD>), dim3(grid), dim3(64), 0, s, p);
+            hipLaunchKernelGGL((tor_main<double, REAL_T, REAL_B, REAL_L, AccAnchor>), dim3(grid), dim3(64), 0, s, p);
         else
             hipLaunchKernelGGL((tor_main<double, REAL_T, REAL_B, REAL_L, AccF64>), dim3(grid), dim3(64), 0, s, p);
     } else {
@@ -1281,7 +1318,7 @@ int main_occupancy(int path)
     if (path == PATH_QUAD)
         return main_occupancy_quad();
     if (path == PATH_REAL)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tor_main<double, REAL_T, REAL_B, REAL_L, AccDD>, 64, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tor_main<double, REAL_T, REAL_B, REAL_L, AccAnchor>, 64, 0);
     else
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, tor_main<c64, CPLX_T, CPLX_B, CPLX_L, AccDD>, 64, 0);
     return e == hipSuccess ? n : 0;
