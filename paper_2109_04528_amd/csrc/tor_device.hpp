@@ -236,15 +236,23 @@ __device__ __forceinline__ const S &blk(const S *node, int nb, int bi, int e)
 }
 
 // triangular index -> (a, b), a >= b, with a(a+1)/2 + b = bi: the mode block
-// of a block index (bidx), or the row and column of a packed entry (pidx)
+// of a block index (bidx), or the row and column of a packed entry (pidx), for
+// bi < 2^20.  The hardware square root (1 ulp) is put right by one step either
+// way; the products are 24-bit ones, which issue at the full rate (32-bit ones
+// at a quarter of it).
 __device__ __forceinline__ void block_ab(int bi, int &a, int &b)
 {
-    a = (int)((sqrtf(8.0f * (float)bi + 1.0f) - 1.0f) * 0.5f);
-    if (a * (a + 1) / 2 > bi)
-        --a;
-    if ((a + 1) * (a + 2) / 2 <= bi)
-        ++a;
-    b = bi - a * (a + 1) / 2;
+    unsigned u = (unsigned)((__builtin_amdgcn_sqrtf(8.0f * (float)bi + 1.0f) - 1.0f) * 0.5f);
+    unsigned t = __umul24(u, u + 1) >> 1;  // u(u+1)/2
+    if (t > (unsigned)bi) {
+        t -= u;
+        --u;
+    } else if (t + u + 1 <= (unsigned)bi) {
+        ++u;
+        t += u;
+    }
+    a = (int)u;
+    b = bi - (int)t;
 }
 
 // ---- wave-uniform broadcast ------------------------------------------------

@@ -478,10 +478,11 @@ __device__ __forceinline__ void restride_node(S *node, int nb, int s, int lane)
 // node (lev, idx) keeps its determinant at (2^(lev-1) - 1) + idx.  Per include
 // node i of level J (record (2^(J-1) - 1) + i, J = 1..B-1) its parent's stored
 // offset and blocks per array and its own stored offset, packed in 64 bits;
-// per block bi of a child (a, b) and its block index bidx(a, b) packed.
+// per block bi of a child (a, b) and its block index bidx(a, b) packed (real
+// path: of the leaf's own include step too, elim_leaf).
 template <int R, int B, int ESZ, int L, int X0>
 struct TierBTables {
-    static constexpr int NV = (1 << B) - 1, NR = (1 << (B - 1)) - 1, NK = NB(R - 1);
+    static constexpr int NV = (1 << B) - 1, NR = (1 << (B - 1)) - 1, NK = NB(R - 1 + X0);
     unsigned long long nodeRec[NR];
     uint32_t blkRec[NK];
     uint16_t srcOff[NV];
@@ -514,7 +515,7 @@ struct TierBTables {
                 nodeRec[t] = (unsigned long long)(srcOff[t] * ESZ) | ((unsigned long long)(16 * srcNB[t]) << 16) |
                              ((unsigned long long)(srcOff[c] * ESZ) << 32);
             }
-        for (int a = 0, bi = 0; a < R - 1; ++a)
+        for (int a = 0, bi = 0; a < R - 1 + X0; ++a)
             for (int b = 0; b <= a; ++b, ++bi)
                 blkRec[bi] = (uint32_t)(16 * bidx(a, b) | (16 * a) << 16 | (16 * b) << 24);
     }
@@ -526,7 +527,7 @@ __device__ __forceinline__ void build_tables(uint16_t *srcOff, uint8_t *srcNB, u
     constexpr int X0 = std::is_same<S, double>::value ? 1 : 0;
     using Tab = TierBTables<R, B, (int)sizeof(S), L, X0>;
     static constexpr Tab tab{};
-    static_assert(Tab::NV <= 64 && Tab::NK <= 64, "one entry per lane");
+    static_assert(Tab::NV <= 64, "one entry per lane");
     if (lane < Tab::NV) {
         srcOff[lane] = tab.srcOff[lane];
         srcNB[lane] = tab.srcNB[lane];
@@ -534,8 +535,8 @@ __device__ __forceinline__ void build_tables(uint16_t *srcOff, uint8_t *srcNB, u
     }
     if (lane < Tab::NR)
         nodeRec[lane] = tab.nodeRec[lane];
-    if (lane < Tab::NK)
-        blkRec[lane] = tab.blkRec[lane];
+    for (int t = lane; t < Tab::NK; t += 64)
+        blkRec[t] = tab.blkRec[t];
 }
 
 // LDS tables of tier B (see build_tables) and its per-node pivot scalars
@@ -627,18 +628,52 @@ __device__ __forceinline__ void tierB_level(const TierB<S> &tb, RT<S> leafDet, i
     // real path: an empty asm hides that the lane index is the same in every
     // leaf, so the node and block indices of the passes of levels 3 and 4 are
     // recomputed per leaf instead of being held in registers across the whole
-    // leaf loop (levels 1 and 2 fit: 249 registers; with the others the
+    // leaf loop (levels 1 and 2 fit: 255 registers; with the others the
     // kernel passes 256 and half the waves go).  The 16-byte paths have
     // registers to spare.
     int ln = lane;
     if constexpr (std::is_same<S, double>::value && J > 2)
         __asm__ volatile("" : "+v"(ln));
+    __builtin_assume((unsigned)ln < 64u);  // node and block by 24-bit products
 #pragma unroll 2
     for (int it0 = 0; it0 < 64 * FULL; it0 += 64)
         pass(it0 + ln);
     if constexpr (TOT % 64 != 0) {
         if (64 * FULL + ln < TOT)
             pass(64 * FULL + ln);
+    }
+    __syncthreads();
+}
+
+// real path: the include step in place on LDS node 0 (R + 1 modes) that makes
+// every second leaf, block coordinates from the table
+template <class S, int R>
+__device__ __forceinline__ void elim_leaf(const TierB<S> &tb, int lane, RT<S> &pdet, int &bad)
+{
+    constexpr int G = EPG((int)sizeof(S)), GPB = 4 / G, ST = 16 * NB(R + 1);
+    char *const lb = reinterpret_cast<char *>(tb.buf);
+    const Piv<S> pv = node_pivot(tb.buf, NB(R + 1), R);
+    pdet = pv.pdet;
+    if (!is_pos(pv.pdet) || !is_pos(pv.inv_a))
+        bad = 1;
+    for (int bi = lane; bi < NB(R); bi += 64) {
+        const uint32_t br = tb.blkRec[bi];
+        const int a16 = (int)((br >> 16) & 0xffu), b16 = (int)(br >> 24);
+        S A[4], Bk[4], H[4], o[4];
+#pragma unroll
+        for (int g = 0; g < GPB; ++g) {
+            const Gran<S> qa = *reinterpret_cast<const Gran<S> *>(lb + a16 + 16 * NB(R) + g * ST);
+            const Gran<S> qb = *reinterpret_cast<const Gran<S> *>(lb + b16 + 16 * NB(R) + g * ST);
+            const Gran<S> qh = *reinterpret_cast<const Gran<S> *>(lb + 16 * bi + g * ST);
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                A[g * G + j] = qa.e[j];
+                Bk[g * G + j] = qb.e[j];
+                H[g * G + j] = qh.e[j];
+            }
+        }
+        elim_math(A, Bk, H, a16 == b16, pv, o);
+        put_block(tb.buf, NB(R + 1), bi, o);
     }
     __syncthreads();
 }
@@ -905,7 +940,7 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
     __shared__ uint16_t srcOff[(1 << (BL + 1)) - 1];
     __shared__ uint8_t srcNB[(1 << (BL + 1)) - 1];
     __shared__ uint8_t srcDet[(1 << (BL + 1)) - 1];
-    __shared__ uint32_t blkRec[NB(R - 1)];
+    __shared__ uint32_t blkRec[NB(R - 1 + X0)];
     __shared__ unsigned long long nodeRec[(1 << BL) - 1];
 
     const int lane = threadIdx.x;
@@ -1023,6 +1058,7 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
             int lane = threadIdx.x;
             if constexpr (std::is_same<S, ddr>::value)
                 __asm__ volatile("" : "+v"(lane));
+            __builtin_assume((unsigned)lane < 64u);
             RT<S> ldet;
             int linc;
             if (x == 0) {
@@ -1060,7 +1096,7 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
                 if (X0 && t == 0) {
                     // the include at level LA-1: its source, the level-(LA-1)
                     // node of this path, is LDS node 0, updated in place
-                    elim_lds<S>(bufB, NB(R + 1), R + 1, lane, pd, bad);
+                    elim_leaf<S, R>(tb, lane, pd, bad);
                 } else {
                     // the deepest slot a later step reads (level LA, or LA-1
                     // when node 0 holds that level) gets the child in LDS
