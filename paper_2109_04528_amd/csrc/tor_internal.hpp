@@ -142,7 +142,6 @@ struct StageDesc {
     int min_cplx;      // minimum modes of the complex form
     void *out;         // the staged form (bytes: staged_bytes)
     StageInfo *info;
-    StageInfo *info2;  // a second copy of the verdict (or null)
 };
 
 // inputs up to this many modes are staged through LDS, each value read once
@@ -211,9 +210,10 @@ hipError_t launch_zeta(const double *t, ddr *g, int nbits, hipStream_t s);
 // i = API mode i) of a staged form of N modes, Tor(O_S) = (-1)^(N-|S|) g[S
 // reversed over N bits] and p(S) = Tor(O_S) sqrt(det(I - O)), each output if
 // its pointer is not null; full receives the sum of the pattern of every mode.
+// det: sqrt(det(I - O)) and, at [2], whether to run at all (0: nothing is written).
 // g is workspace: the sums need not all be stored (tor_zeta.hip).  Null in a
 // host-only build of the runtime without the kernels.
-__attribute__((weak)) hipError_t launch_click_transform(const double *t, ddr *g, int N, int M, const double *sqrt_det,
+__attribute__((weak)) hipError_t launch_click_transform(const double *t, ddr *g, int N, int M, const double *det,
                                                         double *probs, double *tor_hi, double *tor_lo, ddr *full,
                                                         hipStream_t s);
 hipError_t launch_reduce(const ProblemDesc *probs, int nprob, double *results, bool dd, hipStream_t s);
@@ -250,6 +250,36 @@ struct EvalOne {
 // null in a host-only build of the runtime without the kernels, which then
 // takes the general path
 __attribute__((weak)) hipError_t launch_eval_one(const EvalOne &e, hipStream_t s);
+
+// Every pattern of one state, enqueued in one go: staging and sqrt(det(I - O)),
+// the recursive kernel storing its terms, the reduction, the subset sums and
+// the outputs.  What fails on the way keeps the rest from running.
+struct ClickResult {
+    double v[4];     // hi, lo, sum of |t|, flag of the slots
+    double det[2];   // sqrt(det(I - O)), 1 for a failed pivot
+    double ms[2];    // the recursive kernel, the transform
+    ddr full;        // the whole state's subset sum
+    int status, path;  // the staging kernel's verdict
+};
+struct ClickAll {
+    StageDesc st;  // st.info: device memory
+    ProblemDesc P;
+    unsigned long long *counter;  // device: queue head
+    char *scratch;
+    long long stride;
+    int grid;
+    double *terms;  // 2^N, then their sums
+    ddr *g;
+    int N, M;
+    double *det;       // device: sqrt(det(I - O)), 1 for a failed pivot, 1 if the outputs may be written
+    long long *clock;  // device: when the recursive kernel and the transform started
+    double *probs, *tor_hi, *tor_lo;
+    bool dd;
+    ClickResult *result;  // pinned
+};
+__attribute__((weak)) hipError_t launch_click_all(const ClickAll &c, hipStream_t s);
+// its staging kernel (tor_stage.hip)
+hipError_t launch_stage_det(const StageDesc &d, unsigned long long *zero, double *det, hipStream_t s);
 // its staging kernel (tor_stage.hip)
 hipError_t launch_stage_one(const StageDesc &d, unsigned long long *zero, int nzero, hipStream_t s);
 

@@ -1347,6 +1347,80 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
     return hipGetLastError();
 }
 
+// the slots of a click_all launch; sets whether the outputs may be written
+template <bool DD>
+__global__ void __launch_bounds__(RED_THREADS) tor_reduce_click(const StageInfo *gate, ProblemDesc P, double *det,
+                                                                long long *clock, double ms_per_tick, ClickResult *result)
+{
+    __shared__ double r[4];
+    const bool mine = gate->path == PATH_REAL;
+    if (mine)
+        reduce_matrix<DD>(P, r);
+    if (threadIdx.x == 0) {  // the thread that wrote r
+        const double sq = det[0], bad = det[1];
+        det[2] = mine && gate->status == 0 && r[3] == 0.0 && bad == 0.0 && sq > 0.0 ? 1.0 : 0.0;
+        const long long now = wall_clock64();
+        if (mine) {
+            for (int j = 0; j < 4; ++j)
+                st_host(&result->v[j], r[j]);
+            st_host(&result->ms[0], (double)(now - clock[0]) * ms_per_tick);
+        }
+        clock[1] = now;
+        st_host(&result->det[0], sq);
+        st_host(&result->det[1], bad);
+        st_host(&result->status, gate->status);
+        st_host(&result->path, gate->path);
+    }
+}
+
+// the end of a click_all call: the transform's time (an event at either end
+// would put packets of its own between the kernels)
+__global__ void tor_click_end(const long long *clock, double ms_per_tick, ClickResult *result)
+{
+    if (threadIdx.x == 0)
+        st_host(&result->ms[1], (double)(wall_clock64() - clock[1]) * ms_per_tick);
+}
+
+// What bounds a small call is the chain of its launches: six kernels and
+// nothing between them.  A copy each for the state, the descriptors,
+// sqrt(det) and the verdict, an event on either side of two of the kernels and
+// a wait before the transform made the 15 modes' call 111 us, against 69 so
+// (25 modes: 777 and 743).
+hipError_t launch_click_all(const ClickAll &c, hipStream_t s)
+{
+    hipError_t err = launch_stage_det(c.st, c.counter, c.det, s);
+    if (err != hipSuccess)
+        return err;
+    MainParams p{};
+    p.nprob = 1;
+    p.one = c.P;
+    p.total_items = c.P.nroots;
+    p.counter = c.counter;
+    p.scratch = c.scratch;
+    p.scratch_stride = c.stride;
+    p.gate = c.st.info;
+    p.gate_path = PATH_REAL;
+    p.terms = c.terms;
+    p.clock = c.clock;
+    err = launch_main_store(p, c.grid, s);
+    if (err != hipSuccess)
+        return err;
+    const double tick = wall_ms_per_tick();
+    if (c.dd)
+        hipLaunchKernelGGL((tor_reduce_click<true>), dim3(1), dim3(RED_THREADS), 0, s, c.st.info, c.P, c.det, c.clock, tick,
+                           c.result);
+    else
+        hipLaunchKernelGGL((tor_reduce_click<false>), dim3(1), dim3(RED_THREADS), 0, s, c.st.info, c.P, c.det, c.clock, tick,
+                           c.result);
+    err = hipGetLastError();
+    if (err == hipSuccess)
+        err = launch_click_transform(c.terms, c.g, c.N, c.M, c.det, c.probs, c.tor_hi, c.tor_lo, &c.result->full, s);
+    if (err != hipSuccess)
+        return err;
+    hipLaunchKernelGGL(tor_click_end, dim3(1), dim3(64), 0, s, c.clock, tick, c.result);
+    return hipGetLastError();
+}
+
 int main_occupancy(int path)
 {
     int n = 0;

@@ -345,8 +345,7 @@ struct StageIn {
 // writes its status records to ctx->hdown (StageInfo each, from byte 0); *end
 // receives the first workspace byte after the staging area and *down_end the
 // first free byte of ctx->hdown.  stage_collect reads them after the stream
-// has been synchronised.  gate (device memory, or null) receives a copy of the
-// first one, for launches that are enqueued before it is known.
+// has been synchronised.
 // Layout of a staging launch: the image (descriptors, lists, matrices), and
 // the workspace (offsets from its base).  A host matrix given several times
 // (the same pointer, leading dimension and size) is there once: raw_first[i]
@@ -414,13 +413,8 @@ long pack_rows(char *dst, const double *O, long ld, int rows, unsigned sflags)
     return whole ? rows : 0;
 }
 
-// bytes kept free behind the image for a launch of one matrix that is enqueued
-// before the staging kernel has read the image (run_launch's hup_at)
-constexpr size_t LAUNCH_UP_SPARE = 1024;
-
 int stage_enqueue(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, unsigned sflags, int min_cplx,
-                  size_t base, std::vector<Mat> &mats, size_t *end, size_t *down_end, hipStream_t stream = nullptr,
-                  StageInfo *gate = nullptr)
+                  size_t base, std::vector<Mat> &mats, size_t *end, size_t *down_end, hipStream_t stream = nullptr)
 {
     if (!stream)
         stream = ctx->stream;
@@ -437,7 +431,7 @@ int stage_enqueue(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, 
     // it would move them)
     int rc = ensure_ws_keep(ctx, base + L.total, base);
     if (rc == TOR_OK)
-        rc = pin_grow(ctx->hup, ctx->hup_bytes, L.image + LAUNCH_UP_SPARE);
+        rc = pin_grow(ctx->hup, ctx->hup_bytes, L.image);
     if (rc == TOR_OK)  // 256 spare bytes for a caller's own read-back
         rc = pin_grow(ctx->hdown, ctx->hdown_bytes, b_info + 256);
     if (rc != TOR_OK)
@@ -463,7 +457,6 @@ int stage_enqueue(tor_ctx *ctx, const std::vector<StageIn> &in, bool on_device, 
         d.flags = sflags;
         d.min_cplx = min_cplx;
         d.info = (StageInfo *)ctx->hdown + i;
-        d.info2 = i == 0 ? gate : nullptr;
         d.out = x.dst ? (void *)x.dst : (void *)(dbase + out_off[i]);
         if (x.sel) {
             std::memcpy(hsel + sel_at, x.sel, sizeof(int) * (size_t)x.n);
@@ -626,13 +619,10 @@ int lane_ws(LaunchLane &L, size_t bytes)
 // With a lane, the launch goes to the lane's current stream, its workspace
 // and the pinned buffers of its current slot, and the call returns once it
 // is enqueued: the slot's done event follows the reduction into the slot's
-// pinned buffer, which lane_collect then reads.  gate: the launch is enqueued
-// before the staging kernel's verdict is known, runs only if that is `path`,
-// and its descriptors go to byte hup_at of the pinned buffer, behind what the
-// staging kernel has still to read.
+// pinned buffer, which lane_collect then reads.
 int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const std::vector<int> &reduce,
                size_t ws_off, int grid, std::vector<double> *results, float *ms, long long fail_item1 = 0,
-               double *terms = nullptr, LaunchLane *lane = nullptr, const StageInfo *gate = nullptr, size_t hup_at = 0)
+               LaunchLane *lane = nullptr)
 {
     const int count = (int)descs.size();
     long long total = 0, stack = 0;
@@ -668,23 +658,19 @@ int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const st
     // the zeroed queue counter after them: one copy from pinned memory (the
     // previous use of the buffer has been synchronised)
     const size_t up = Lo.b_probs + Lo.b_red + sizeof(unsigned long long);
-    if (hup_at > 0)  // what lies below is still to be read, so nothing may move
-        rc = hup_at + up <= hup_bytes && sizeof(double) * 4 * (size_t)nred <= hdown_bytes ? TOR_OK : TOR_E_NOMEM;
-    else
-        rc = pin_grow(hup, hup_bytes, up);
-    if (rc == TOR_OK && hup_at == 0)
+    rc = pin_grow(hup, hup_bytes, up);
+    if (rc == TOR_OK)
         rc = pin_grow(hdown, hdown_bytes, sizeof(double) * 4 * (size_t)std::max(nred, 1));
     if (rc != TOR_OK)
         return rc;
-    char *const image = hup + hup_at;
-    std::memset(image, 0, up);
-    std::memcpy(image, descs.data(), sizeof(ProblemDesc) * count);
+    std::memset(hup, 0, up);
+    std::memcpy(hup, descs.data(), sizeof(ProblemDesc) * count);
     if (nred)
-        std::memcpy(image + Lo.b_probs, red.data(), sizeof(ProblemDesc) * nred);
+        std::memcpy(hup + Lo.b_probs, red.data(), sizeof(ProblemDesc) * nred);
 
     hipError_t e = hipSetDevice(ctx->device);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(dProbs, image, up, hipMemcpyHostToDevice, stream);
+        e = hipMemcpyAsync(dProbs, hup, up, hipMemcpyHostToDevice, stream);
     MainParams mp{};
     mp.probs = (const ProblemDesc *)dProbs;
     mp.nprob = count;
@@ -693,10 +679,7 @@ int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const st
     mp.scratch = dScr;
     mp.scratch_stride = stride;
     mp.fail_item1 = fail_item1;
-    mp.terms = terms;
     mp.tickets_only = lane != nullptr;
-    mp.gate = gate;
-    mp.gate_path = path;
     // the double-double factor always sums in double-double
     const bool dd = ctx->opt.accum != TOR_ACCUM_FP64 || path == PATH_QUAD;
     if (e == hipSuccess)
@@ -704,8 +687,7 @@ int run_launch(tor_ctx *ctx, int path, std::vector<ProblemDesc> &descs, const st
     // no more persistent waves than queue items: a launch of few roots (a
     // small matrix) does not pay for starting the whole grid
     if (e == hipSuccess && total > 0)
-        e = terms ? launch_main_store(mp, (int)std::min<long long>(grid, total), stream)
-                  : launch_main(path, dd, mp, (int)std::min<long long>(grid, total), stream);
+        e = launch_main(path, dd, mp, (int)std::min<long long>(grid, total), stream);
     if (e == hipSuccess)
         e = hipEventRecord(ev1, stream);  // device_ms: the main kernel alone
     const double *hres = (const double *)hdown;
@@ -1507,7 +1489,7 @@ int serve_round(tor_ctx *ctx, const ServeCfg &cfg, int path, std::vector<Request
             ++rec.used[i]->flights;
             rec.used[i]->quick_flight |= quick;
         }
-    const int rc = run_launch(ctx, path, descs, rec.red, 0, grid, nullptr, nullptr, 0, nullptr, &lane);
+    const int rc = run_launch(ctx, path, descs, rec.red, 0, grid, nullptr, nullptr, 0, &lane);
     if (rc != TOR_OK) {
         // its requests may hold roots in a launch queued before it
         for (hipStream_t st : {lane.stream, lane.side, lane.wide})
@@ -2358,7 +2340,7 @@ int tor_click_all(tor_ctx *ctx, int M, const double *O, long ld, double *probs, 
     // the terms are stored by the FP64 kernel of the real quadrature form
     if (ctx->opt.flags & (TOR_FORCE_COMPLEX | TOR_FACTOR_DD))
         return TOR_E_INVAL;
-    if (!launch_click_transform)
+    if (!launch_click_all)
         return TOR_E_DEVICE;
     if (M == 0) {  // the empty pattern of a 0-mode state: Tor = 1, p = 1
         const double one[2] = {1.0, 0.0};
@@ -2393,136 +2375,116 @@ int tor_click_all(tor_ctx *ctx, int M, const double *O, long ld, double *probs, 
         return TOR_OK;
     }
     std::lock_guard<std::mutex> g(ctx->mu);
-    const int m2 = 2 * M;
-    const bool dev = (ctx->opt.flags & TOR_INPUT_DEVICE) != 0;
-    const size_t bO = dev ? 0 : align_up(sizeof(c64) * (size_t)m2 * m2, 256);
-    const size_t bScr = align_up(sizeof(c64) * (size_t)m2 * m2, 256);
-    const size_t oGate = bO + bScr + 256, base = oGate + 256;
-    std::vector<StageIn> in(1);
-    in[0].n = M;
-    in[0].M = M;
     const unsigned sfl = stage_flags(ctx->opt.flags);
-    // The workspace is sized before anything is enqueued.  After the staged
-    // matrix: root slots, the 2^N terms, their subset sums, staging arrays
-    // for large outputs that go to the host (none with TOR_OUTPUT_DEVICE;
-    // small ones are written straight to pinned memory), then what run_launch
-    // needs.  The real path is the only one that stores terms, so its size and
-    // depth are known before the staging kernel's verdict: the recursive
-    // kernel is enqueued behind it and returns at once without that path.
-    const StageLayout SL = stage_layout(in, true, sfl, CPLX_R);
-    const size_t end = base + SL.total;
+    // Workspace: verdict, sqrt(det), clocks and queue head, the staged matrix,
+    // root slots, the 2^N terms, their subset sums, staging arrays for large
+    // outputs that go to the host (none with TOR_OUTPUT_DEVICE; small ones are
+    // written straight to pinned memory), per-wave stacks.  The real path is
+    // the only one that stores terms, so its size and depth are known before
+    // the staging kernel's verdict and the whole call is enqueued at once.
     const int N = std::max(M, REAL_R);
     const int k = choose_k(ctx, N, PATH_REAL);
     const long long nS = 1ll << N, nP = 1ll << M;
-    const size_t oSlots = align_up(end, 256);
+    const size_t oDet = 256, oClock = 512, oForm = 1024;
+    const size_t oSlots = oForm + align_up(staged_bytes(M, sfl, CPLX_R), 256);
     const size_t oTerms = align_up(oSlots + sizeof(double) * 4 * ((size_t)1 << k), 256);
     const size_t oG = align_up(oTerms + sizeof(double) * (size_t)nS, 256);
     const size_t oOut = align_up(oG + sizeof(ddr) * (size_t)nS, 256);
     const size_t out_bytes = dev_out ? 0 : ((probs ? 1 : 0) + (tor_hi ? 2 : 0)) * sizeof(double) * (size_t)nP;
     const bool pinned_out = out_bytes > 0 && out_bytes <= CLICK_PINNED_BYTES;
     const size_t off = align_up(oOut + (pinned_out ? 0 : out_bytes), 256);
-    const long long stack = wave_stack_bytes(PATH_REAL, N, k);
     const int fit = std::max(1, std::min(main_store_occupancy(), ctx->fit[PATH_REAL]));
-    const int grid = ctx->num_cu * fit;
-    int rc = ensure_ws_keep(ctx, off + launch_layout(1, 1, stack).total(grid), 0);
+    ClickAll c{};
+    c.stride = std::max(wave_stack_bytes(PATH_REAL, N, k), 256ll);
+    c.grid = (int)std::min<long long>((long long)ctx->num_cu * fit, 1ll << k);
+    int rc = ensure_ws_keep(ctx, off + (size_t)c.stride * (size_t)c.grid, 0);
+    // pinned: the result, then the outputs
+    constexpr size_t RES = 256;
+    static_assert(sizeof(ClickResult) <= RES, "");
+    if (rc == TOR_OK)
+        rc = pin_grow(ctx->hout, ctx->hout_bytes, RES + (pinned_out ? out_bytes : 0));
+    if (rc == TOR_OK && !(ctx->opt.flags & TOR_INPUT_DEVICE))
+        rc = pin_grow(ctx->hstate, ctx->hstate_bytes, sizeof(c64) * raw_entries(2 * M, sfl));
     if (rc != TOR_OK)
         return rc;
+    char *const ws = ctx->ws;
+    c.st.n = c.st.M = M;
+    c.st.flags = sfl;
+    c.st.min_cplx = CPLX_R;
+    c.st.O = O;
+    c.st.ld = ld;
+    if (!(ctx->opt.flags & TOR_INPUT_DEVICE)) {  // read across the bus
+        c.st.O = (const double *)ctx->hstate;
+        c.st.ld = pack_rows(ctx->hstate, O, ld, 2 * M, sfl);
+    }
+    c.st.info = (StageInfo *)ws;
+    c.st.out = ws + oForm;
+    c.P.C = c.st.out;
+    c.P.slots = (double *)(ws + oSlots);
+    c.P.N = N;
+    c.P.k = k;
+    c.P.nroots = 1ll << k;
+    c.det = (double *)(ws + oDet);
+    c.clock = (long long *)(ws + oClock);
+    c.counter = (unsigned long long *)(ws + oClock + 128);
+    c.scratch = ws + off;
+    c.terms = (double *)(ws + oTerms);
+    c.g = (ddr *)(ws + oG);
+    c.N = N;
+    c.M = M;
+    c.dd = ctx->opt.accum != TOR_ACCUM_FP64;
+    ClickResult *res = (ClickResult *)ctx->hout;
+    c.result = res;
+    // where the kernel writes: the caller's device arrays, pinned memory, or
+    // the workspace (the latter two then copied to the caller's host arrays)
+    double *stage = pinned_out ? (double *)(ctx->hout + RES) : (double *)(ws + oOut);
+    c.probs = probs ? (dev_out ? probs : stage) : nullptr;
+    c.tor_hi = tor_hi ? (dev_out ? tor_hi : stage + (probs ? nP : 0)) : nullptr;
+    c.tor_lo = tor_lo ? (dev_out ? tor_lo : stage + (probs ? nP : 0) + nP) : nullptr;
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess)
         return hip_status(e);
-    const double *dO = O;
-    long dld = ld;
-    rc = upload_state(ctx, M, sfl, dO, dld);
-    if (rc != TOR_OK)
-        return rc;
-    double *dDet = (double *)(ctx->ws + bO + bScr);
-    StageInfo *gate = (StageInfo *)(ctx->ws + oGate);
-    in[0].O = dO;
-    in[0].ld = dld;
-    std::vector<Mat> mats;
-    size_t got_end = 0, down = 0;
-    rc = stage_enqueue(ctx, in, true, sfl, CPLX_R, base, mats, &got_end, &down, nullptr, gate);
-    // pinned, in a buffer of its own (run_launch uses the other two):
-    // sqrt(det), the whole state's sum, the verdict, then the outputs
-    if (rc == TOR_OK && (rc = pin_grow(ctx->hout, ctx->hout_bytes, 256 + (pinned_out ? out_bytes : 0))) == TOR_OK)
-        rc = hip_status(launch_sqrt_det(dO, dld, M, (c64 *)(ctx->ws + bO), dDet, ctx->stream));
-    if (rc != TOR_OK) {
-        (void)hipStreamSynchronize(ctx->stream);  // the state's copy
-        return rc;
-    }
-    double *hDet = (double *)ctx->hout;
-    ddr *hFull = (ddr *)(ctx->hout + 16);
-    StageInfo *hInfo = (StageInfo *)(ctx->hout + 64);
-    e = hipMemcpyAsync(hDet, dDet, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(hInfo, gate, sizeof(StageInfo), hipMemcpyDeviceToHost, ctx->stream);
-    if (e != hipSuccess) {
-        (void)hipStreamSynchronize(ctx->stream);
-        return hip_status(e);
-    }
-    double *dTerms = (double *)(ctx->ws + oTerms);
-    ddr *dG = (ddr *)(ctx->ws + oG);
-    std::vector<ProblemDesc> descs(1);
-    ProblemDesc &d = descs[0];
-    d.C = mat_ptr(ctx, mats[0]);
-    d.slots = (double *)(ctx->ws + oSlots);
-    d.N = N;
-    d.k = k;
-    d.root_begin = 0;
-    d.nroots = 1ll << k;
-    std::vector<double> res;
-    float ms_main = 0.f, ms_zeta = 0.f;
-    rc = run_launch(ctx, PATH_REAL, descs, std::vector<int>{0}, off, grid, &res, &ms_main, 0, dTerms, nullptr, gate,
-                    align_up(SL.image, 256));
-    if (rc != TOR_OK) {
-        (void)hipStreamSynchronize(ctx->stream);
-        return rc;
-    }
-    if (hDet[1] != 0.0 || !(hDet[0] > 0.0))
+    e = launch_click_all(c, ctx->stream);
+    const hipError_t e2 = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess || e2 != hipSuccess)
+        return hip_status(e != hipSuccess ? e : e2);
+    if (res->det[1] != 0.0 || !(res->det[0] > 0.0))
         return TOR_E_NOT_PD;
-    if (hInfo->status != 0 || hInfo->path != PATH_REAL)
+    if (res->status != 0 || res->path != PATH_REAL)
         return TOR_E_INVAL;  // bad values, or O lacks the Gaussian-state block structure
-    mats[0].path = PATH_REAL;
-    mats[0].N = N;
-    if (res[3] >= SLOT_NOT_PD)
+    if (res->v[3] >= SLOT_NOT_PD)
         return TOR_E_NOT_PD;
-    if (res[3] > 0.0)
+    if (res->v[3] > 0.0)
         return TOR_E_NUMERIC;
-    // where the kernel writes: the caller's device arrays, pinned memory, or
-    // the workspace (the latter two then copied to the caller's host arrays)
-    double *stage = pinned_out ? (double *)(ctx->hout + 256) : (double *)(ctx->ws + oOut);
-    double *pP = probs ? (dev_out ? probs : stage) : nullptr;
-    double *pH = tor_hi ? (dev_out ? tor_hi : stage + (probs ? nP : 0)) : nullptr;
-    double *pL = tor_lo ? (dev_out ? tor_lo : stage + (probs ? nP : 0) + nP) : nullptr;
-    // the whole state's Tor for out: the subset sum of the pattern of every
-    // mode, with the sign (-1)^(N-M) that turns a subset sum into a Torontonian
-    e = hipEventRecord(ctx->ev0, ctx->stream);
-    if (e == hipSuccess)
-        e = launch_click_transform(dTerms, dG, N, M, dDet, pP, pH, pL, hFull, ctx->stream);
-    if (e == hipSuccess)
-        e = hipEventRecord(ctx->ev1, ctx->stream);
     struct Out {
         double *to;
         const double *from;
     };
-    const Out outs[3] = {{probs, pP}, {tor_hi, pH}, {tor_lo, pL}};
-    for (const Out &o : outs)
-        if (e == hipSuccess && o.to && !dev_out && !pinned_out)
+    const Out outs[3] = {{probs, c.probs}, {tor_hi, c.tor_hi}, {tor_lo, c.tor_lo}};
+    for (const Out &o : outs) {
+        if (!o.to || dev_out)
+            continue;
+        if (pinned_out)
+            std::memcpy(o.to, o.from, sizeof(double) * nP);
+        else if (e == hipSuccess)
             e = hipMemcpyAsync(o.to, o.from, sizeof(double) * nP, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess)
+    }
+    if (e == hipSuccess && !dev_out && !pinned_out)
         e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess)
         return hip_status(e);
-    for (const Out &o : outs)
-        if (o.to && pinned_out)
-            std::memcpy(o.to, o.from, sizeof(double) * nP);
-    (void)hipEventElapsedTime(&ms_zeta, ctx->ev0, ctx->ev1);
     if (out) {
         // the result of the whole state (every mode clicks), with the sum of
-        // |t| over all subsets and the device time of both steps
+        // |t| over all subsets and the device time of both steps.  Its Tor is the
+        // subset sum of the pattern of every mode, with the sign (-1)^(N-M)
+        // that turns a subset sum into a Torontonian.
+        Mat m;
+        m.n = M;
+        m.N = N;
+        m.path = PATH_REAL;
         const double sg = ((N - M) & 1) ? -1.0 : 1.0;
-        const double r[4] = {sg * hFull->hi, sg * hFull->lo, res[2], 0.0};
-        fill_result(mats[0], PATH_REAL, r, ms_main + ms_zeta, out);
+        const double r[4] = {sg * res->full.hi, sg * res->full.lo, res->v[2], 0.0};
+        fill_result(m, PATH_REAL, r, (float)(res->ms[0] + res->ms[1]), out);
     }
     return TOR_OK;
 }

@@ -193,10 +193,9 @@ constexpr int STAGE_LDS_ENTRIES = NB(2 * STAGE_LDS_MODES);
 // over the input (across the bus for a host matrix), one block-wide maximum,
 // one pass over the output.
 template <int NT>
-__device__ __forceinline__ void stage_matrix(const StageDesc &D)
+__device__ __forceinline__ void stage_matrix(const StageDesc &D, c64 *tri)
 {
     __shared__ unsigned long long best[5];
-    __shared__ c64 tri[STAGE_LDS_ENTRIES];
     const int t = threadIdx.x;
     if (t < 5)
         best[t] = 0ull;
@@ -274,12 +273,8 @@ __device__ __forceinline__ void stage_matrix(const StageDesc &D)
                   : path == PATH_REAL ? max(n, REAL_R)
                   : path == PATH_QUAD ? max(n, QUAD_R)
                                       : max(n, D.min_cplx);
-    if (t == 0) {
-        const StageInfo info{status, status ? -1 : path, N, 0, sqrt(cmax2)};
-        *D.info = info;
-        if (D.info2)
-            *D.info2 = info;
-    }
+    if (t == 0)
+        *D.info = StageInfo{status, status ? -1 : path, N, 0, sqrt(cmax2)};
     if (status != 0)
         return;
 
@@ -321,7 +316,8 @@ __device__ __forceinline__ void stage_matrix(const StageDesc &D)
 template <int NT>
 __global__ void __launch_bounds__(NT) tor_stage(const StageDesc *descs)
 {
-    stage_matrix<NT>(descs[blockIdx.x]);
+    __shared__ c64 tri[STAGE_LDS_ENTRIES];
+    stage_matrix<NT>(descs[blockIdx.x], tri);
 }
 
 // one matrix, its descriptor a kernel argument; clears the queue heads of the
@@ -331,7 +327,8 @@ __global__ void __launch_bounds__(NT) tor_stage_one(StageDesc D, unsigned long l
 {
     if ((int)threadIdx.x < nzero)
         zero[threadIdx.x] = 0ull;
-    stage_matrix<NT>(D);
+    __shared__ c64 tri[STAGE_LDS_ENTRIES];
+    stage_matrix<NT>(D, tri);
 }
 
 // sqrt(det(I - O)) of an M-mode O (device, leading dimension ld, 0: packed
@@ -343,10 +340,11 @@ __global__ void __launch_bounds__(NT) tor_stage_one(StageDesc D, unsigned long l
 // out[0] receives the root of the product of the pivots' determinants, out[1]
 // = 1 when a pivot was not positive (or not a number).  What bounds it is the
 // chain of M such steps, about 0.3 us each.
+// A: entry e of block (a, b), a >= b, at [e][bidx(a, b)].
+typedef c64 DetBlocks[NB(STAGE_LDS_MODES)];
 template <int NT>
-__global__ void __launch_bounds__(NT) tor_sqrt_det_lds(const double *O, long ld, int M, double *out)
+__device__ __forceinline__ void sqrt_det_lds(const double *O, long ld, int M, double *out, DetBlocks *A)
 {
-    __shared__ c64 A[4][NB(STAGE_LDS_MODES)];  // entry e of block (a, b), a >= b, at [e][bidx(a, b)]
     const int t = threadIdx.x;
     const View v{O, ld, M, nullptr, M, nullptr};
     for (int q = t; q < 4 * NB(M); q += NT) {
@@ -390,6 +388,34 @@ __global__ void __launch_bounds__(NT) tor_sqrt_det_lds(const double *O, long ld,
     if (t == 0) {
         out[0] = prod;
         out[1] = bad ? 1.0 : 0.0;
+    }
+}
+
+template <int NT>
+__global__ void __launch_bounds__(NT) tor_sqrt_det_lds(const double *O, long ld, int M, double *out)
+{
+    __shared__ DetBlocks A[4];
+    sqrt_det_lds<NT>(O, ld, M, out, A);
+}
+
+// A state whose every pattern is wanted: staged by one workgroup while a
+// second one forms sqrt(det(I - O)), which alone takes longer than the staging
+// (at 15 modes one launch of 12 us in place of 6.5 + 11 and the gap between
+// them); clears the queue head of the launch that follows.
+template <int NT, int DET_NT>
+__global__ void __launch_bounds__(NT) tor_stage_det(StageDesc D, unsigned long long *zero, double *det)
+{
+    static_assert(DET_NT <= NT, "");
+    constexpr int SZ = STAGE_LDS_ENTRIES > 4 * NB(STAGE_LDS_MODES) ? STAGE_LDS_ENTRIES : 4 * NB(STAGE_LDS_MODES);
+    __shared__ c64 buf[SZ];
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0)
+            *zero = 0ull;
+        stage_matrix<NT>(D, buf);
+    } else {
+        if (__builtin_amdgcn_readfirstlane((int)threadIdx.x) >= DET_NT)
+            return;  // whole waves: a barrier waits for the others alone
+        sqrt_det_lds<DET_NT>(D.O, D.ld, D.M, det, reinterpret_cast<DetBlocks *>(buf));
     }
 }
 
@@ -463,6 +489,14 @@ hipError_t launch_stage_one(const StageDesc &d, unsigned long long *zero, int nz
         hipLaunchKernelGGL((tor_stage_one<256>), dim3(1), dim3(256), 0, s, d, zero, nzero);
     else
         hipLaunchKernelGGL((tor_stage_one<STAGE_THREADS>), dim3(1), dim3(STAGE_THREADS), 0, s, d, zero, nzero);
+    return hipGetLastError();
+}
+
+hipError_t launch_stage_det(const StageDesc &d, unsigned long long *zero, double *det, hipStream_t s)
+{
+    if (d.M > STAGE_LDS_MODES || d.sel)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL((tor_stage_det<STAGE_THREADS, DET_LDS_THREADS>), dim3(2), dim3(STAGE_THREADS), 0, s, d, zero, det);
     return hipGetLastError();
 }
 

@@ -69,11 +69,26 @@ __device__ __forceinline__ void dd_acc(double &ah, double &al, double bh, double
     two_sum(s, e, ah, al);
 }
 
+// Where a click call's outputs go (null: not wanted).  full: the sum of the
+// pattern of every mode.  go: 0 where an earlier step of the call failed (null:
+// there is none); the kernels then leave everything as it is, so that the whole
+// call is enqueued at once (a wait for the verdict between the recursive kernel
+// and the transform left the device idle for 10 us).
+struct ClickOut {
+    const double *sqrt_det;
+    double *probs, *tor_hi, *tor_lo;
+    ddr *full;
+    const double *go;
+};
+__device__ __forceinline__ bool stopped(const double *go) { return go && *go == 0.0; }
+
 // bits 0 .. nb-1 of a block of 2^nb entries (nb <= ZB), one bit at a time in
 // LDS, terms in, double-double out; ZT threads
 template <int ZB, int ZT>
-__global__ void __launch_bounds__(ZT) tor_zeta_lds(const double *t, ddr *g, int nb)
+__global__ void __launch_bounds__(ZT) tor_zeta_lds(const double *t, ddr *g, int nb, const double *go)
 {
+    if (stopped(go))
+        return;
     __shared__ double hs[1 << ZB], ls[1 << ZB];
     const int size = 1 << nb;
     const long long base = (long long)blockIdx.x << nb;
@@ -113,8 +128,10 @@ __global__ void __launch_bounds__(ZT) tor_zeta_lds(const double *t, ddr *g, int 
 // M = 32, 256 threads of 16 entries gave 159.8 ms per call, 512 of 8 161.0, 1024
 // of 4 164.8, one bit at a time 167.5 to 168.8 (M = 24: 0.56 against 0.58 ms).
 template <int ZB, int ZT, int RB>
-__global__ void __launch_bounds__(ZT) tor_zeta_lds_r(const double *t, ddr *g)
+__global__ void __launch_bounds__(ZT) tor_zeta_lds_r(const double *t, ddr *g, const double *go)
 {
+    if (stopped(go))
+        return;
     static_assert((ZT << RB) == (1 << ZB) && ZB % RB == 0, "a block is ZT threads of 2^RB entries");
     constexpr int E = 1 << RB;
     __shared__ double hs[1 << ZB], ls[1 << ZB];
@@ -166,8 +183,10 @@ __global__ void __launch_bounds__(ZT) tor_zeta_lds_r(const double *t, ddr *g)
 // NT: streaming (non-temporal) loads and stores, for sums too large to stay
 // in the caches between passes
 template <bool NT>
-__global__ void __launch_bounds__(256) tor_zeta_bits(ddr *g, int nbits, int b0, int nb)
+__global__ void __launch_bounds__(256) tor_zeta_bits(ddr *g, int nbits, int b0, int nb, const double *go)
 {
+    if (stopped(go))
+        return;
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= (1ll << (nbits - nb)))
         return;
@@ -207,13 +226,6 @@ __global__ void __launch_bounds__(256) tor_zeta_bits(ddr *g, int nbits, int b0, 
         }
 }
 
-// where a click call's outputs go (null: not wanted); full: the sum of the
-// pattern of every mode
-struct ClickOut {
-    const double *sqrt_det;
-    double *probs, *tor_hi, *tor_lo;
-    ddr *full;
-};
 
 // one pattern's outputs from its subset sum v
 __device__ __forceinline__ void put_pattern(long long S, int N, int M, ddr v, double sq, const ClickOut &o)
@@ -243,6 +255,8 @@ __device__ __forceinline__ void put_pattern(long long S, int N, int M, ddr v, do
 template <int HB, bool OUT, bool NT>
 __global__ void __launch_bounds__(256) tor_zeta_tile(ddr *g, int N, int b0, ClickOut out)
 {
+    if (stopped(out.go))
+        return;
     static_assert(HB >= 3 && HB <= 8, "two rounds of up to 4 bits, runs of 16 entries at least");
     constexpr int CB = ZB_MAX - HB, E = 16, RB = 4;
     __shared__ double hs[1 << ZB_MAX], ls[1 << ZB_MAX];
@@ -340,6 +354,8 @@ __global__ void __launch_bounds__(256) tor_zeta_tile(ddr *g, int N, int b0, Clic
 constexpr int TA = 5;
 __global__ void __launch_bounds__(256) tor_click_out_tiled(const ddr *g, int N, ClickOut out)
 {
+    if (stopped(out.go))
+        return;
     __shared__ double th[1 << TA][(1 << TA) + 1], tl[1 << TA][(1 << TA) + 1];
     const long long mid = blockIdx.x;
     const int nm = N - 2 * TA;
@@ -364,6 +380,8 @@ __global__ void __launch_bounds__(256) tor_click_out_tiled(const ddr *g, int N, 
 // one thread per pattern S < 2^M (any M <= N): a gather, for the padded forms
 __global__ void __launch_bounds__(256) tor_click_out(const ddr *g, int N, int M, ClickOut out)
 {
+    if (stopped(out.go))
+        return;
     const long long S = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (S >= (1ll << M))
         return;
@@ -376,17 +394,17 @@ __global__ void __launch_bounds__(256) tor_click_out(const ddr *g, int N, int M,
 namespace {
 
 // the first nb bits (10 and 12 in registers and LDS, others bit by bit in LDS)
-hipError_t first_stage(const double *t, ddr *g, int nbits, int nb, hipStream_t s)
+hipError_t first_stage(const double *t, ddr *g, int nbits, int nb, const double *go, hipStream_t s)
 {
     const dim3 grid((unsigned)(1ll << (nbits - nb)));
     if (nb == 12)
-        hipLaunchKernelGGL((tor_zeta_lds_r<12, 256, 4>), grid, dim3(256), 0, s, t, g);
+        hipLaunchKernelGGL((tor_zeta_lds_r<12, 256, 4>), grid, dim3(256), 0, s, t, g, go);
     else if (nb == 10)
-        hipLaunchKernelGGL((tor_zeta_lds_r<10, 256, 2>), grid, dim3(256), 0, s, t, g);
+        hipLaunchKernelGGL((tor_zeta_lds_r<10, 256, 2>), grid, dim3(256), 0, s, t, g, go);
     else if (nb == 11)
-        hipLaunchKernelGGL((tor_zeta_lds<11, 512>), grid, dim3(512), 0, s, t, g, nb);
+        hipLaunchKernelGGL((tor_zeta_lds<11, 512>), grid, dim3(512), 0, s, t, g, nb, go);
     else
-        hipLaunchKernelGGL((tor_zeta_lds<10, 256>), grid, dim3(256), 0, s, t, g, nb);
+        hipLaunchKernelGGL((tor_zeta_lds<10, 256>), grid, dim3(256), 0, s, t, g, nb, go);
     return hipGetLastError();
 }
 
@@ -397,14 +415,14 @@ hipError_t first_stage(const double *t, ddr *g, int nbits, int nb, hipStream_t s
 bool streaming(int nbits) { return nbits >= 26; }
 
 // bits b0 .. b0+w-1, w <= ZG, in registers
-hipError_t bits_pass(ddr *g, int nbits, int b0, int w, hipStream_t s)
+hipError_t bits_pass(ddr *g, int nbits, int b0, int w, const double *go, hipStream_t s)
 {
     const long long threads = 1ll << (nbits - w);
     const dim3 grid((unsigned)((threads + 255) / 256));
     if (streaming(nbits))
-        hipLaunchKernelGGL((tor_zeta_bits<true>), grid, dim3(256), 0, s, g, nbits, b0, w);
+        hipLaunchKernelGGL((tor_zeta_bits<true>), grid, dim3(256), 0, s, g, nbits, b0, w, go);
     else
-        hipLaunchKernelGGL((tor_zeta_bits<false>), grid, dim3(256), 0, s, g, nbits, b0, w);
+        hipLaunchKernelGGL((tor_zeta_bits<false>), grid, dim3(256), 0, s, g, nbits, b0, w, go);
     return hipGetLastError();
 }
 
@@ -437,12 +455,14 @@ hipError_t tile_pass(ddr *g, int nbits, int b0, int w, const ClickOut &o, hipStr
 // bits b0 .. b1-1 in as few passes as there are: 8 by tiles, up to 5 in
 // registers (which read and write nothing but their own entries, in longer
 // runs), 6 and 7 by tiles
-hipError_t middle(ddr *g, int nbits, int b0, int b1, hipStream_t s)
+hipError_t middle(ddr *g, int nbits, int b0, int b1, const double *go, hipStream_t s)
 {
     hipError_t e = hipSuccess;
+    ClickOut o{};
+    o.go = go;
     while (e == hipSuccess && b0 < b1) {
         const int left = b1 - b0, w = left <= ZG ? left : left <= 8 ? left : left <= 8 + ZG ? left - 8 : 8;
-        e = w <= ZG ? bits_pass(g, nbits, b0, w, s) : tile_pass<false>(g, nbits, b0, w, ClickOut{}, s);
+        e = w <= ZG ? bits_pass(g, nbits, b0, w, go, s) : tile_pass<false>(g, nbits, b0, w, o, s);
         b0 += w;
     }
     return e;
@@ -450,28 +470,30 @@ hipError_t middle(ddr *g, int nbits, int b0, int b1, hipStream_t s)
 
 }  // namespace
 
-hipError_t launch_zeta(const double *t, ddr *g, int nbits, hipStream_t s)
+static hipError_t subset_sums(const double *t, ddr *g, int nbits, const double *go, hipStream_t s)
 {
     const int nb = nbits < ZB_MAX ? nbits : ZB_MAX;
-    const hipError_t e = first_stage(t, g, nbits, nb, s);
-    return e == hipSuccess ? middle(g, nbits, nb, nbits, s) : e;
+    const hipError_t e = first_stage(t, g, nbits, nb, go, s);
+    return e == hipSuccess ? middle(g, nbits, nb, nbits, go, s) : e;
 }
 
-hipError_t launch_click_transform(const double *t, ddr *g, int N, int M, const double *sqrt_det, double *probs,
+hipError_t launch_zeta(const double *t, ddr *g, int nbits, hipStream_t s) { return subset_sums(t, g, nbits, nullptr, s); }
+
+hipError_t launch_click_transform(const double *t, ddr *g, int N, int M, const double *det, double *probs,
                                   double *tor_hi, double *tor_lo, ddr *full, hipStream_t s)
 {
-    const ClickOut o{sqrt_det, probs, tor_hi, tor_lo, full};
+    const ClickOut o{det, probs, tor_hi, tor_lo, full, det + 2};
     if (M == N && N >= 13) {
         // the last pass takes 8 bits, or what a first stage of 10 leaves (its
         // 1024-entry blocks keep more loads in flight than 4096-entry ones)
         const int last = N - 10 < 8 ? N - 10 : 8;
         const int first = N - last <= 10 ? 10 : ZB_MAX < N - last ? ZB_MAX : N - last;
-        hipError_t e = first_stage(t, g, N, first, s);
+        hipError_t e = first_stage(t, g, N, first, o.go, s);
         if (e == hipSuccess)
-            e = middle(g, N, first, N - last, s);
+            e = middle(g, N, first, N - last, o.go, s);
         return e == hipSuccess ? tile_pass<true>(g, N, N - last, last, o, s) : e;
     }
-    hipError_t e = launch_zeta(t, g, N, s);
+    hipError_t e = subset_sums(t, g, N, o.go, s);
     if (e != hipSuccess)
         return e;
     if (M == N && N >= 2 * TA) {
