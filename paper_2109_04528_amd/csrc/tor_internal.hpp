@@ -79,8 +79,11 @@ struct MainParams {
                                   // signed term of each subset, indexed by subset
                                   // (bit N-1-l = decision at level l); else null
     const StageInfo *gate;        // run only if the staging kernel gave gate_path (null: always)
-    EvalResult *result;           // a launch of one root: its slot's values go here too (or null)
-    unsigned long long done;      // with result: the last kernel of its chain, which announces this number
+    EvalResult *result;           // a launch of one matrix with few roots: its sum goes here (or null)
+    unsigned long long *finished; // with result: roots that are done, zero before the launch
+    unsigned long long done;      // with result: the number to announce (or 0)
+    int done_gated;               // the last launch of its chain: it announces also where the gate
+    int quiet_path;               // keeps it from running, but for this path's own kernel having done so
     long long *clock;             // the device clock at the kernel's start goes here (or null)
     double ms_per_tick;           // of that clock
     int tickets_only;             // blocks may start late: no item is any block's own
@@ -232,8 +235,9 @@ constexpr int FMA_PROBE_CHAINS = 16;
 // matrix is staged already (st.info holds the verdict).
 struct EvalOne {
     bool stage;
+    bool early;                    // an unused path's kernels may end after the result is there
     StageDesc st;                  // st.info: device memory
-    unsigned long long *counters;  // device: a queue head per run
+    unsigned long long *counters;  // device: 2 queue heads, 2 counts of finished roots
     int nrun;
     struct Run {
         int path;

@@ -923,6 +923,79 @@ __device__ __forceinline__ void announce(EvalResult *r, const StageInfo *gate, u
     __hip_atomic_store(&r->done, done, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Agent-scope accesses: what another wave of the same launch reads, on
+// whichever die it runs.
+template <class V>
+__device__ __forceinline__ void st_agent(V *p, V v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class V>
+__device__ __forceinline__ V ld_agent(const V *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <bool DD>
+__device__ inline void red_step(double &h, double &l, double &ab, double &bad, int off)
+{
+    const double oh = __shfl_xor(h, off), ol = __shfl_xor(l, off);
+    if (DD)
+        dd_add2(h, l, oh, ol);
+    else
+        h += oh;
+    ab += __shfl_xor(ab, off);
+    bad = fmax(bad, __shfl_xor(bad, off));
+}
+
+// The end of a root of a lone evaluation with at most RESULT_ROOTS of them
+// (its slot is written): the wave that ends last sums the slots, in
+// the order of the reduction kernel (whose threads and waves beyond them add
+// zeros), and announces the result, instead of a launch for that alone: 17
+// modes 34.2 us a call against 37.8, 13 Hermitian ones 29.5 against 31.9.  More roots than lanes keep the
+// kernel of their own: they would all meet at this one counter (13 ns each),
+// and one wave would add several slots a lane.
+template <bool DD>
+__device__ __forceinline__ void finish_root(const __attribute__((address_space(4))) MainParams *prm, const double *slots, int lane)
+{
+    const int nroots = (int)prm->total_items;
+    if (nroots > 1) {
+        // the slot is out before it is counted
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        unsigned long long before = 0;
+        if (lane == 0)
+            before = __hip_atomic_fetch_add(prm->finished, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (bcast_first(before) + 1 < (unsigned long long)nroots)
+            return;
+    }
+    double h = 0.0, l = 0.0, ab = 0.0, bad = 0.0;
+    if (lane < nroots) {
+        const double *s = slots + 4 * lane;
+        const double s0 = ld_agent(s), s1 = ld_agent(s + 1);
+        ab = ld_agent(s + 2);
+        bad = ld_agent(s + 3);
+        if (DD)
+            dd_add2(h, l, s0, s1);
+        else
+            h = s0;
+    }
+#pragma unroll 1
+    for (int off = 32; off >= 1; off >>= 1)
+        red_step<DD>(h, l, ab, bad, off);
+    if (DD)
+        dd_add2(h, l, 0.0, 0.0);
+    if (lane == 0) {
+        st_host(&prm->result->v[0], h);
+        st_host(&prm->result->v[1], l);
+        st_host(&prm->result->v[2], ab);
+        st_host(&prm->result->v[3], bad);
+        st_host(&prm->result->ms, (double)(wall_clock64() - ld_agent(prm->clock)) * prm->ms_per_tick);
+        if (prm->done)
+            announce(prm->result, prm->gate, prm->done);
+    }
+}
+
 template <class S, int T, int B, int L, class Acc>
 __global__ void __launch_bounds__(64) tor_main(MainParams prm)
 {
@@ -946,12 +1019,12 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
     const int lane = threadIdx.x;
     if (prm.gate && prm.gate->path != prm.gate_path) {
         // the matrix has another path, or is not valid
-        if (prm.done && blockIdx.x == 0 && lane == 0)
+        if (prm.done_gated && prm.gate->path != prm.quiet_path && blockIdx.x == 0 && lane == 0)
             announce(prm.result, prm.gate, prm.done);
         return;
     }
     if (prm.clock && blockIdx.x == 0 && lane == 0)
-        *prm.clock = wall_clock64();
+        st_agent(prm.clock, (long long)wall_clock64());
     build_tables<S, R, BL + 1, L>(srcOff, srcNB, srcDet, nodeRec, blkRec, lane);
     __syncthreads();
     const TierB<S> tb{bufB, srcOff, srcNB, srcDet, nodeRec, blkRec, nInv, nBa, ndet};
@@ -1141,17 +1214,19 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
             // again (the host's recovery from a numeric failure) is idempotent
             const bool forced = item + 1 == prm.fail_item1;
             double *sl = P.slots + 4 * root;
-            sl[0] = forced ? __builtin_nan("") : h;
-            sl[1] = l;
-            sl[2] = ab;
-            sl[3] = anybad ? SLOT_NOT_PD : (forced || !__builtin_isfinite(h)) ? SLOT_NUMERIC : 0.0;
-            if (prm.result) {  // the matrix's only root: the reduction would give the same
-                for (int j = 0; j < 4; ++j)
-                    st_host(&prm.result->v[j], sl[j]);
-                st_host(&prm.result->ms, (double)(wall_clock64() - *prm.clock) * prm.ms_per_tick);
-                if (prm.done)
-                    announce(prm.result, prm.gate, prm.done);
-            }
+            const double v[4] = {forced ? __builtin_nan("") : h, l, ab,
+                                 anybad ? SLOT_NOT_PD : (forced || !__builtin_isfinite(h)) ? SLOT_NUMERIC : 0.0};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                st_agent(&sl[j], v[j]);
+        }
+        if constexpr (!std::is_same<Acc, AccStore>::value) {
+            // these arguments are read here, not held from the kernel's start
+            typedef const __attribute__((address_space(4))) MainParams CParams;
+            CParams *late = (CParams *)__builtin_amdgcn_kernarg_segment_ptr();
+            __asm__ volatile("" : "+s"(late));
+            if (late->result)
+                finish_root<Acc::kDD>(late, P.slots, lane);
         }
     }
 }
@@ -1161,18 +1236,6 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
 // ... in index order, then the threads are combined by a fixed tree (within
 // each wave, then across the waves), so the result does not depend on timing.
 constexpr int RED_THREADS = 1024;
-
-template <bool DD>
-__device__ inline void red_step(double &h, double &l, double &ab, double &bad, int off)
-{
-    const double oh = __shfl_xor(h, off), ol = __shfl_xor(l, off);
-    if (DD)
-        dd_add2(h, l, oh, ol);
-    else
-        h += oh;
-    ab += __shfl_xor(ab, off);
-    bad = fmax(bad, __shfl_xor(bad, off));
-}
 
 template <bool DD>
 __device__ __forceinline__ void reduce_matrix(const ProblemDesc &P, double *result)
@@ -1226,11 +1289,12 @@ __global__ void __launch_bounds__(RED_THREADS) tor_reduce(const ProblemDesc *pro
 }
 
 // one matrix, of the path the staging kernel gave it (a or b); the end of its
-// chain
+// chain (quiet_path: that path's own kernel has announced the result)
 template <bool DD>
 __global__ void __launch_bounds__(RED_THREADS) tor_reduce_one(const StageInfo *gate, int path_a, ProblemDesc a, int path_b,
-                                                              ProblemDesc b, const long long *clock, double ms_per_tick,
-                                                              EvalResult *result, unsigned long long done)
+                                                              ProblemDesc b, int quiet_path, const long long *clock,
+                                                              double ms_per_tick, EvalResult *result,
+                                                              unsigned long long done)
 {
     __shared__ double r[4];
     const int path = gate->path;
@@ -1248,7 +1312,8 @@ __global__ void __launch_bounds__(RED_THREADS) tor_reduce_one(const StageInfo *g
                 st_host(&result->v[j], r[j]);
             st_host(&result->ms, ms);
         }
-        announce(result, gate, done);
+        if (path != quiet_path)
+            announce(result, gate, done);
     }
 }
 
@@ -1308,16 +1373,24 @@ static double wall_ms_per_tick()
     return v;
 }
 
+// roots of a lone evaluation up to which its last wave forms the result
+// (finish_root): one a lane
+constexpr int RESULT_ROOTS = 64;
+
 hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
 {
     if (e.nrun < 1 || e.nrun > 2)
         return hipErrorInvalidValue;
-    hipError_t err = e.stage ? launch_stage_one(e.st, e.counters, e.nrun, s) : launch_zero(e.counters, e.nrun, s);
-    bool reduce = false;
+    hipError_t err = e.stage ? launch_stage_one(e.st, e.counters, 4, s) : launch_zero(e.counters, 4, s);
+    // the paths whose roots a kernel of their own has to sum
+    int red[2] = {-2, -2}, quiet = -2;
     for (int i = 0; i < e.nrun; ++i)
-        reduce |= e.run[i].P.nroots > 1;
+        if (e.run[i].P.nroots > RESULT_ROOTS)
+            red[i] = e.run[i].path;
+    const bool reduce = red[0] >= 0 || red[1] >= 0;
     for (int i = 0; i < e.nrun && err == hipSuccess; ++i) {
         const EvalOne::Run &r = e.run[i];
+        const bool last = !reduce && i == e.nrun - 1;
         MainParams p{};
         p.nprob = 1;
         p.one = r.P;
@@ -1327,22 +1400,29 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
         p.scratch_stride = r.stride;
         p.gate = e.st.info;
         p.gate_path = r.path;
-        p.result = r.P.nroots == 1 ? e.result : nullptr;
-        p.done = !reduce && i == e.nrun - 1 ? e.done : 0;
+        if (red[i] < 0) {
+            // the result is announced as soon as it is there, or by the
+            // chain's last kernel
+            p.result = e.result;
+            p.finished = e.counters + 2 + i;
+            p.done = e.early || last ? e.done : 0;
+            if (e.early && !last)
+                quiet = r.path;
+        }
+        p.done_gated = last;
+        p.quiet_path = quiet;
         p.clock = e.clock;
         p.ms_per_tick = wall_ms_per_tick();
         err = launch_main(r.path, e.dd, p, r.grid, s);
     }
     if (err != hipSuccess || !reduce)
         return err;
-    // a path of one root has written its result: it takes no part here
-    const EvalOne::Run &a = e.run[0], &b = e.run[e.nrun - 1];
-    const int pa = a.P.nroots > 1 ? a.path : -2, pb = b.P.nroots > 1 ? b.path : -2;
+    const ProblemDesc &a = e.run[0].P, &b = e.run[e.nrun - 1].P;
     if (e.dd)
-        hipLaunchKernelGGL((tor_reduce_one<true>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, pa, a.P, pb, b.P, e.clock,
+        hipLaunchKernelGGL((tor_reduce_one<true>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, red[0], a, red[1], b, quiet, e.clock,
                            wall_ms_per_tick(), e.result, e.done);
     else
-        hipLaunchKernelGGL((tor_reduce_one<false>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, pa, a.P, pb, b.P, e.clock,
+        hipLaunchKernelGGL((tor_reduce_one<false>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, red[0], a, red[1], b, quiet, e.clock,
                            wall_ms_per_tick(), e.result, e.done);
     return hipGetLastError();
 }
