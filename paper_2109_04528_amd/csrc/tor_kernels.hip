@@ -59,10 +59,23 @@ namespace tor {
 // the start of each of its granule arrays, as a 16-byte slot modulo 8 (and
 // modulo 16), differs from that of the other nodes read by the same group of
 // lanes; failing that, to the place with the fewest such clashes.
+// 16-byte scalars (X0 = 0): when level BL is formed, only the first NB(R-BL+1)
+// blocks of a stored node are still read, so the last two nodes of that level lie
+// in the granule arrays of nodes 0 and 1, behind those blocks, with the host
+// node's array stride (these two of the eight, for no lane group meets on a bank
+// then).  What node 0 has left behind that holds the pivots of levels 2 on.
+// Together that is 22624 -> 20448 B a wave (double-double 22880 -> 20432) and
+// an eighth wave per CU, two on each SIMD, with the split depths that suit 2048
+// waves: complex n = 27 1331 -> 1185 us a call, n = 30 9.5 -> 8.57 ms,
+// double-double n = 23 265 -> 243 us, n = 30 22.6 -> 20.9 ms.
 template <int R, int BL, int ESZ, int L, int X0 = 0>
 struct NodePlacement {
     static constexpr int NN = 1 << BL;
+    static constexpr int LIVE = NB(R - BL + 1);  // blocks the parents of level BL have
+    static constexpr bool TUCK = X0 == 0;
+    static_assert(!TUCK || (BL >= 3 && LIVE + NB(R - BL) <= NB(R - 1)), "room behind the live blocks of nodes 0 and 1");
     int off[NN + 1];
+    int nb[NN];  // blocks per granule array
     // the level-BL view whose stored node is t: the include node i of
     // level j is followed by excludes only
     static constexpr int reader(int t)
@@ -82,7 +95,7 @@ struct NodePlacement {
             ++lev;
         return lev;
     }
-    constexpr NodePlacement() : off{}
+    constexpr NodePlacement() : off{}, nb{}
     {
         constexpr int gpb = 4 / EPG(ESZ);          // granule arrays per node
         constexpr int acc = ESZ == 8 ? 8 : 16;     // bytes per lane per access
@@ -92,20 +105,25 @@ struct NodePlacement {
         int slot[NN] = {};
         int pos = 0;
         for (int t = 0; t < NN; ++t) {
-            const int nb = t == 0 ? NB(R + X0) : NB(R - level(t));
+            nb[t] = t == 0 ? NB(R + X0) : NB(R - level(t));
+            if (TUCK && t >= NN - 2) {
+                const int host = NN - 1 - t;
+                nb[t] = nb[host];
+                off[t] = off[host] + 16 * LIVE;
+                continue;
+            }
             const int b0 = (pos + 15) & ~15;
             int best = b0, bestc = 1 << 30;
             for (int k = 0; k < 16 && bestc > 0; ++k) {
                 const int st = (b0 >> 4) + k;
                 int c = 0;
                 for (int u = 0; u < t; ++u) {
-                    const int unb = u == 0 ? NB(R + X0) : NB(R - level(u));
                     for (int mdl = 0; mdl < 2; ++mdl) {
                         const int G = grp[mdl] > 1 ? grp[mdl] : 1;
                         if (reader(u) / G != reader(t) / G)
                             continue;
                         for (int g = 0; g < gpb; ++g)
-                            if ((st + g * nb) % mods[mdl] == (slot[u] + g * unb) % mods[mdl])
+                            if ((st + g * nb[t]) % mods[mdl] == (slot[u] + g * nb[u]) % mods[mdl])
                                 ++c;
                     }
                 }
@@ -477,7 +495,8 @@ __device__ __forceinline__ void restride_node(S *node, int nb, int s, int lane)
 // array, and the slot of its determinant (0xff: the tier-A leaf).  The include
 // node (lev, idx) keeps its determinant at (2^(lev-1) - 1) + idx.  Per include
 // node i of level J (record (2^(J-1) - 1) + i, J = 1..B-1) its parent's stored
-// offset and blocks per array and its own stored offset, packed in 64 bits;
+// offset and blocks per array and its own stored offset, packed in 64 bits (its
+// own blocks per array too where they differ within the level, NodePlacement);
 // per block bi of a child (a, b) and its block index bidx(a, b) packed (real
 // path: of the leaf's own include step too, elim_leaf).
 template <int R, int B, int ESZ, int L, int X0>
@@ -502,7 +521,7 @@ struct TierBTables {
                     ++tz;
                 const int lev = jl - tz, idx = (i >> tz) >> 1;
                 off = place.off[(1 << (lev - 1)) + idx] / ESZ;
-                nb = NB(R - lev);
+                nb = place.nb[(1 << (lev - 1)) + idx];
                 det = (1 << (lev - 1)) - 1 + idx;
             }
             srcOff[t] = (uint16_t)off;
@@ -513,7 +532,8 @@ struct TierBTables {
             for (int i = 0; i < 1 << (J - 1); ++i) {
                 const int t = (1 << (J - 1)) - 1 + i, c = (1 << J) - 1 + 2 * i + 1;
                 nodeRec[t] = (unsigned long long)(srcOff[t] * ESZ) | ((unsigned long long)(16 * srcNB[t]) << 16) |
-                             ((unsigned long long)(srcOff[c] * ESZ) << 32);
+                             ((unsigned long long)(srcOff[c] * ESZ) << 32) |
+                             (X0 == 0 && J == B - 1 ? (unsigned long long)(16 * srcNB[c]) << 48 : 0ull);
             }
         for (int a = 0, bi = 0; a < R - 1 + X0; ++a)
             for (int b = 0; b <= a; ++b, ++bi)
@@ -546,15 +566,61 @@ struct TierB {
     const uint16_t *srcOff; // per view: offset of its stored node
     const uint8_t *srcNB;   // per view: blocks per granule array of that node
     const uint8_t *srcDet;  // per view: determinant slot (0xff: tier-A leaf)
-    const unsigned long long *nodeRec;  // per include node, bytes: parent | its granule array stride << 16 | own << 32
+    const unsigned long long *nodeRec;  // per include node, bytes: parent | its granule array stride << 16 | own << 32, 48
     const uint32_t *blkRec;             // block index, bytes: 16 bidx(a, b) | 16 a << 16 | 16 b << 24
-    RT<S> *nInv;            // per include node of a level: 1/alpha, 1/gamma1
-    S *nBa;                 // per include node of a level: beta/alpha
-    RT<S> *ndet;            // per include node: running determinant
+    RT<S> *ndet;            // per include node: running determinant (det_at)
+    RT<S> *nInvS;           // per include node of a level: 1/alpha, 1/gamma1 (real path; pivot_slots)
+    S *nBaS;                // per include node of a level: beta/alpha (the same)
 };
 
+// Where the pivots of a level are kept between its two phases: arrays of their
+// own on the real path; on the 16-byte paths behind the blocks of node 0 that
+// level 1 was the last to read, 1/alpha, 1/gamma1 and beta/alpha in one granule
+// array each, and level 1's own in the last node of level BL but the two tucked
+// away, which is not there yet.  The double-double factor's determinants of level
+// BL lie in the fourth array.
+template <class S, int R, int BL, int L>
+struct TuckedPivots {
+    using Place = NodePlacement<R, BL, (int)sizeof(S), L, 0>;
+    static constexpr Place place{};
+    static constexpr int AT = 16 * (Place::LIVE + NB(R - BL)), ROOM = 16 * NB(R) - AT;
+    static_assert((int)sizeof(S) << (BL - 1) <= ROOM && (int)sizeof(RT<S>) << (BL - 1) <= ROOM, "one entry per include node");
+    // array a of level J, from the start of the buffer
+    static constexpr int at(int J, int a)
+    {
+        return J == 1 ? place.off[Place::NN] - 64 * NB(R - BL) + 16 * a : place.off[0] + 16 * NB(R) * a + AT;
+    }
+};
+// 1/alpha, 1/gamma1 and beta/alpha of include node i of level J
+template <class S, int R, int J, int BL, int L>
+__device__ __forceinline__ void pivot_slots(const TierB<S> &tb, int i, RT<S> *&inv_a, RT<S> *&inv_g, S *&ba)
+{
+    if constexpr (std::is_same<S, double>::value) {
+        inv_a = tb.nInvS + 2 * i;
+        inv_g = tb.nInvS + 2 * i + 1;
+        ba = tb.nBaS + i;
+    } else {
+        using P = TuckedPivots<S, R, BL, L>;
+        char *const lb = reinterpret_cast<char *>(tb.buf);
+        inv_a = reinterpret_cast<RT<S> *>(lb + P::at(J, 0)) + i;
+        inv_g = reinterpret_cast<RT<S> *>(lb + P::at(J, 1)) + i;
+        ba = reinterpret_cast<S *>(lb + P::at(J, 2)) + i;
+    }
+}
+// the running determinant of include node d (levels in order)
+template <class S, int R, int BL, int L>
+__device__ __forceinline__ RT<S> *det_at(const TierB<S> &tb, int d)
+{
+    if constexpr (std::is_same<S, ddr>::value) {
+        constexpr int LAST = (1 << (BL - 1)) - 1;  // the first one of level BL
+        if (d >= LAST)
+            return reinterpret_cast<RT<S> *>(reinterpret_cast<char *>(tb.buf) + TuckedPivots<S, R, BL, L>::at(2, 3)) + (d - LAST);
+    }
+    return tb.ndet + d;
+}
+
 // tier B, level J: every include node of level J from its parent of level J-1
-template <class S, int R, int J>
+template <class S, int R, int J, int BL, int L>
 __device__ __forceinline__ void tierB_level(const TierB<S> &tb, RT<S> leafDet, int lane, int &bad)
 {
     constexpr int m = R - J;          // pivot mode of the parent (it has m+1 modes)
@@ -563,12 +629,15 @@ __device__ __forceinline__ void tierB_level(const TierB<S> &tb, RT<S> leafDet, i
     if (lane < NN) {
         const S *par = tb.buf + tb.srcOff[NN - 1 + lane];
         const int di = tb.srcDet[NN - 1 + lane];
-        const RT<S> pdp = di == 0xff ? leafDet : tb.ndet[di];
+        const RT<S> pdp = di == 0xff ? leafDet : *det_at<S, R, BL, L>(tb, di);
         const Piv<S> pq = node_pivot(par, (int)tb.srcNB[NN - 1 + lane], m);
-        tb.nInv[2 * lane] = pq.inv_a;
-        tb.nInv[2 * lane + 1] = pq.inv_g;
-        tb.nBa[lane] = pq.ba;
-        tb.ndet[NN - 1 + lane] = rmul(pdp, pq.pdet);
+        RT<S> *pa, *pg;
+        S *pb;
+        pivot_slots<S, R, J, BL, L>(tb, lane, pa, pg, pb);
+        *pa = pq.inv_a;
+        *pg = pq.inv_g;
+        *pb = pq.ba;
+        *det_at<S, R, BL, L>(tb, NN - 1 + lane) = rmul(pdp, pq.pdet);
         if (!is_pos(pq.pdet) || !is_pos(pq.inv_a))
             bad = 1;
     }
@@ -585,6 +654,7 @@ __device__ __forceinline__ void tierB_level(const TierB<S> &tb, RT<S> leafDet, i
     // cycles; the 8-byte path keeps packed nodes (its passes hold two
     // granules per block, and the extra index registers cost it waves).
     constexpr bool AL = !std::is_same<S, double>::value;
+    constexpr bool TUCK = AL && J == BL;  // nodes of several array strides
     constexpr int NS = AL ? (NBO + 15) / 16 * 16 : NBO;  // lanes per node in a pass
     auto pass = [&](int it) {
         const int i = (int)((unsigned)it / NS), bi = it - i * NS;
@@ -592,12 +662,16 @@ __device__ __forceinline__ void tierB_level(const TierB<S> &tb, RT<S> leafDet, i
             return;
         const unsigned long long rec = tb.nodeRec[NN - 1 + i];
         const uint32_t br = tb.blkRec[bi];
-        const int par = (int)(rec & 0xffffu), st = (int)((rec >> 16) & 0xffffu), cof = (int)(rec >> 32);
+        const int par = (int)(rec & 0xffffu), st = (int)((rec >> 16) & 0xffffu), cof = TUCK ? (int)((rec >> 32) & 0xffffu) : (int)(rec >> 32);
+        const int cst = TUCK ? (int)(rec >> 48) : 16 * NBO;  // the child's granule arrays
         const int a16 = (int)((br >> 16) & 0xffu), b16 = (int)(br >> 24), h16 = (int)(br & 0xffffu);
         Piv<S> pq;
-        pq.inv_a = tb.nInv[2 * i];
-        pq.inv_g = tb.nInv[2 * i + 1];
-        pq.ba = tb.nBa[i];
+        RT<S> *qpa, *qpg;
+        S *qpb;
+        pivot_slots<S, R, J, BL, L>(tb, i, qpa, qpg, qpb);
+        pq.inv_a = *qpa;
+        pq.inv_g = *qpg;
+        pq.ba = *qpb;
         S A[4], Bk[4], H[4], o[4];
         const char *pa = lb + par + a16 + 16 * NB(m), *pb = lb + par + b16 + 16 * NB(m), *ph = lb + par + h16;
 #pragma unroll
@@ -621,7 +695,7 @@ __device__ __forceinline__ void tierB_level(const TierB<S> &tb, RT<S> leafDet, i
 #pragma unroll
             for (int j = 0; j < EPG((int)sizeof(S)); ++j)
                 q.e[j] = o[g * EPG((int)sizeof(S)) + j];
-            *reinterpret_cast<Gran<S> *>(pc + g * 16 * NBO) = q;
+            *reinterpret_cast<Gran<S> *>(pc + g * cst) = q;
         }
     };
     constexpr int TOT = NN * NS, FULL = TOT / 64;
@@ -678,12 +752,12 @@ __device__ __forceinline__ void elim_leaf(const TierB<S> &tb, int lane, RT<S> &p
     __syncthreads();
 }
 
-template <class S, int R, int J, int B>
+template <class S, int R, int J, int BL, int L>
 __device__ __forceinline__ void tierB(const TierB<S> &tb, RT<S> leafDet, int lane, int &bad)
 {
-    if constexpr (J < B) {
-        tierB_level<S, R, J>(tb, leafDet, lane, bad);
-        tierB<S, R, J + 1, B>(tb, leafDet, lane, bad);
+    if constexpr (J <= BL) {
+        tierB_level<S, R, J, BL, L>(tb, leafDet, lane, bad);
+        tierB<S, R, J + 1, BL, L>(tb, leafDet, lane, bad);
     }
 }
 
@@ -811,7 +885,7 @@ __device__ __forceinline__ void tierC_terms(const TierB<S> &tb, RT<S> leafDet, i
     const S *src = tb.buf + tb.srcOff[NP + ip];
     const int snb = tb.srcNB[NP + ip];
     const int di = tb.srcDet[NP + ip];
-    RT<S> det = di == 0xff ? leafDet : tb.ndet[di];
+    RT<S> det = di == 0xff ? leafDet : *det_at<S, T + B, B - L, L>(tb, di);
     const bool inc1 = (lane >> (L - 1)) & 1;  // first lane level
     const bool inc0 = lane & 1;               // second (L == 2)
 
@@ -1007,9 +1081,9 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
     constexpr int X0 = std::is_same<S, double>::value ? 1 : 0;
     constexpr int kBufScalars = NodePlacement<R, BL, (int)sizeof(S), L, X0>{}.off[1 << BL] / (int)sizeof(S);
     __shared__ S bufB[kBufScalars];
-    __shared__ S nBa[NN_MAX];
+    __shared__ S nBa[NN_MAX];          // real path alone (TuckedPivots)
     __shared__ RT<S> nInv[2 * NN_MAX];
-    __shared__ RT<S> ndet[1 << BL];
+    __shared__ RT<S> ndet[std::is_same<S, ddr>::value ? NN_MAX - 1 : (1 << BL) - 1];
     __shared__ uint16_t srcOff[(1 << (BL + 1)) - 1];
     __shared__ uint8_t srcNB[(1 << (BL + 1)) - 1];
     __shared__ uint8_t srcDet[(1 << (BL + 1)) - 1];
@@ -1027,7 +1101,7 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
         st_agent(prm.clock, (long long)wall_clock64());
     build_tables<S, R, BL + 1, L>(srcOff, srcNB, srcDet, nodeRec, blkRec, lane);
     __syncthreads();
-    const TierB<S> tb{bufB, srcOff, srcNB, srcDet, nodeRec, blkRec, nInv, nBa, ndet};
+    const TierB<S> tb{bufB, srcOff, srcNB, srcDet, nodeRec, blkRec, ndet, X0 ? nInv : nullptr, X0 ? nBa : nullptr};
     S *wscr = reinterpret_cast<S *>(prm.scratch + (long long)blockIdx.x * prm.scratch_stride);
 
     // The first item of each wave is its own block's; the queue counter hands
@@ -1192,7 +1266,7 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
                 const unsigned long long rrev = k ? __builtin_bitreverse64((unsigned long long)root) >> (64 - k) : 0ull;
                 acc.begin_leaf(prm.terms + ((rrev << (N - k)) | ((unsigned long long)x << R) | ((unsigned long long)lane << T)));
             }
-            tierB<S, R, 1, BL + 1>(tb, ldet, lane, bad);
+            tierB<S, R, 1, BL, L>(tb, ldet, lane, bad);
             tierC<S, T, B, L, Acc>(tb, ldet, linc, N, lane, acc, bad, root == (1ll << k) - 1 && x == nleaf - 1);
             __syncthreads();
         }

@@ -212,22 +212,29 @@ int choose_k(const tor_ctx *ctx, int N, int path)
     // place.  From there on the time goes to whichever is the smaller loss:
     // the waves that share a SIMD run at different speeds, which several
     // roots per wave even out, and every root pays its own set-up (up to k
-    // eliminations).  Kernel times on a 256-CU part, us:
-    if (path == PATH_REAL && default_grid(ctx, path) == 1 << g) {
-        // 2048 waves: n = 22 (LA = 11) 29.1 at k = 11, 29.8 at 10, 40.6 at 9;
+    // eliminations).  Kernel times on a 256-CU part (2048 waves, g = 11), us:
+    if (default_grid(ctx, path) == 1 << g) {
+        // real n = 22 (LA = 11) 29.1 at k = 11, 29.8 at 10, 40.6 at 9;
         // n = 24 67.1 at 11, 77.0 at 10, 82.4 at 12, 117 at 13; n = 27 366 at
         // 11, 376 at 13, 418 at 12; n = 28 692 at 13, 726 at 11, 812 at 12;
         // n = 30 2558 at 13, 2631 at 14, 2800 at 11, 3207 at 12 (two roots per
         // wave end worst: a wave's second root starts when the others' do)
-        return std::min(LA, LA <= g + 5 ? g : g + 2);
+        if (path == PATH_REAL)
+            return std::min(LA, LA <= g + 5 ? g : g + 2);
+        // 16-byte paths: at g - 1 each wave of the smallest ones has its SIMD to
+        // itself.  complex n = 20 (LA = 11) 27.5 at 10, 29.4 at 11; n = 21 41 at
+        // either; n = 23 99 at 11, 114 at 10, 116 at 12; n = 26 632 at 11, 634 at
+        // 13, 647 at 12; n = 27 1180 at 13, 1190 at 11; n = 30 8565 at 13, 8698 at
+        // 14, 9523 at 12.  Double-double, whose set-up takes longest: n = 21 81.4
+        // at 10, 83.5 at 11; n = 23 227 at 11, 244 at 12; n = 24 (LA = 15) 398 at
+        // 12, 408 at 11, 471 at 13; n = 26 1413 at 12, 1483 at 11, 1579 at 13; n =
+        // 30 20 947 at 12, 20 983 at 13, 23 597 at 11
+        if (path == PATH_QUAD)
+            return std::min(LA, LA <= g + 1 ? g - 1 : LA <= g + 3 ? g : g + 1);
+        return std::min(LA, LA <= g + 1 ? g - 1 : LA <= g + 6 ? g : g + 2);
     }
-    // 1792 waves on the 16-byte paths (and a grid cut to less than a power of
-    // two of waves): at k = g a few waves run a second root alone, so k = g - 1.
-    // complex n = 23 (LA = 14) 116 at k = 10, 126 at 11, 125 at 12; n = 24 202
-    // at 12, 213 at 10, 221 at 11; n = 25 357 at 12, 413 at 10 and 11; n = 27
-    // 1310 at 14, 1318 at 12, 1334 at 13.  Double-double, whose leaves take
-    // longest: n = 25 (LA = 16) 896 at 10, 925 at 13, 1026 at 11; n = 26 1699 at
-    // 14, 1747 at 10, 1763 at 13
+    // a grid of less than a power of two of waves: at k = g a few waves run a
+    // second root alone, so k = g - 1 (measured with 1792 waves)
     const int one = g - 1;
     if (path == PATH_QUAD)
         return std::min(LA, LA <= g + 5 ? one : g + 3);
@@ -960,15 +967,18 @@ void fill_result(const Mat &st, int path, const double *r, float ms, tor_result 
 // wave, as before; x = 13.3 [13] 83 against 142; x = 14.0 [14] 105 against
 // 214; x = 15.2 (n = 27) [14] 228 against 291; x = 16.3 (256 of n = 8..22) [15]
 // 425 against 469; x = 21.2 (512 of n = 12..26) [16] 11 711 against 12 598.
-// Complex x = 11.5 [11] 78 against 160, x = 16.5 [14] 1414 against 1602;
-// double-double x = 12.2 [13] 238 against 348, x = 17.9 [13] 9712 against 9867.
+// Complex x = 9.4 [10] 34, 54 at 9; x = 12.0 [12] 97, 116 at 13; x = 14.9 [13]
+// 547, 567 at 12, 585 at 14; x = 16.0 [14] 1092, 1111 at 13; double-double x =
+// 12.0 [12] 214, 234 at 13; x = 16.3 [13] 3431, 3578 at 14.
 int batch_root_lg(int path, double x)
 {
     if (path == PATH_REAL)
         return x <= 15.1 ? std::min(14, (int)std::floor(x + 0.6)) : std::min(16, (int)std::floor(x - 1.1));
-    if (x < 12.0)
-        return std::min(11, (int)std::floor(x + (path == PATH_QUAD ? 0.4 : 0.6)));
-    return path == PATH_CPLX && x >= 16.3 ? 14 : 13;
+    if (x < 11.9)
+        return std::min(11, (int)std::floor(x + (path == PATH_QUAD ? 0.4 : 0.7)));
+    if (path == PATH_QUAD)
+        return x < 12.7 ? 12 : 13;
+    return x < 13.9 ? 12 : x < 15.6 ? 13 : 14;
 }
 
 // Split depths for a launch of several matrices: roots of about equal work
