@@ -15,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtor.so")
 ARCH = os.environ.get("TOR_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["tor_kernels.hip", "tor_compare.hip", "tor_stage.hip", "tor_zeta.hip", "tor_probe.hip", "tor_runtime.cpp"]
+SOURCES = ["tor_kernels.hip", "tor_compare.hip", "tor_stage.hip", "tor_small.hip", "tor_zeta.hip", "tor_probe.hip",
+           "tor_runtime.cpp"]
 # the double-double factor's kernel: its own translation unit, compiled with
 # the AMDGPU scheduler's register-pressure trackers, which schedule it about
 # 4 % faster (the FP64 kernels gain nothing from them)

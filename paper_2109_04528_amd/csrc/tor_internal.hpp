@@ -284,7 +284,11 @@ struct ClickAll {
 __attribute__((weak)) hipError_t launch_click_all(const ClickAll &c, hipStream_t s);
 // its staging kernel (tor_stage.hip)
 hipError_t launch_stage_det(const StageDesc &d, unsigned long long *zero, double *det, hipStream_t s);
-// its staging kernel (tor_stage.hip)
+// its staging kernel (tor_stage.hip), or staging and the recursive kernel of one
+// path in one launch where that has a single root (tor_small.hip)
+constexpr int SMALL_MODES = 11;
+hipError_t launch_small(int path, const MainParams &p, const StageDesc &d, unsigned long long *zero, int nzero,
+                        hipStream_t s);
 hipError_t launch_stage_one(const StageDesc &d, unsigned long long *zero, int nzero, hipStream_t s);
 
 // defined in tor_stage.hip

@@ -37,8 +37,9 @@
 // written to the root's partial slot; a second kernel sums the slots of each
 // matrix in index order.
 // The double-double factor's instantiation of the main kernel is built in
-// tor_kernels_quad.hip, which includes this file with
-// TOR_KERNELS_TEMPLATES_ONLY defined (templates only, no launchers).
+// tor_kernels_quad.hip, and the one-launch form of the smallest evaluations in
+// tor_small.hip; both include this file with TOR_KERNELS_TEMPLATES_ONLY defined
+// (templates only, no launchers).
 #include <type_traits>
 
 #include "tor_device.hpp"
@@ -1070,8 +1071,9 @@ __device__ __forceinline__ void finish_root(const __attribute__((address_space(4
     }
 }
 
+// one wave of a launch; prm is the first of the kernel's arguments
 template <class S, int T, int B, int L, class Acc>
-__global__ void __launch_bounds__(64) tor_main(MainParams prm)
+__device__ __forceinline__ void main_wave(const MainParams &prm)
 {
     constexpr int R = T + B;
     constexpr int BL = B - L;                // levels expanded in LDS
@@ -1305,6 +1307,12 @@ __global__ void __launch_bounds__(64) tor_main(MainParams prm)
     }
 }
 
+template <class S, int T, int B, int L, class Acc>
+__global__ void __launch_bounds__(64) tor_main(MainParams prm)
+{
+    main_wave<S, T, B, L, Acc>(prm);
+}
+
 // ---------------------------------------------------------------------------
 // per-matrix sum of the root slots: thread t takes roots t, t + RED_THREADS,
 // ... in index order, then the threads are combined by a fixed tree (within
@@ -1455,7 +1463,12 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
 {
     if (e.nrun < 1 || e.nrun > 2)
         return hipErrorInvalidValue;
-    hipError_t err = e.stage ? launch_stage_one(e.st, e.counters, 4, s) : launch_zero(e.counters, 4, s);
+    // one leaf: the first path's kernel stages the matrix itself (the FP64 sum,
+    // an option, has no such kernel)
+    const bool small = e.stage && e.dd && e.run[0].P.nroots == 1 && e.st.n <= SMALL_MODES;
+    hipError_t err = small      ? hipSuccess
+                     : e.stage ? launch_stage_one(e.st, e.counters, 4, s)
+                               : launch_zero(e.counters, 4, s);
     // the paths whose roots a kernel of their own has to sum
     int red[2] = {-2, -2}, quiet = -2;
     for (int i = 0; i < e.nrun; ++i)
@@ -1487,7 +1500,7 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
         p.quiet_path = quiet;
         p.clock = e.clock;
         p.ms_per_tick = wall_ms_per_tick();
-        err = launch_main(r.path, e.dd, p, r.grid, s);
+        err = small && i == 0 ? launch_small(r.path, p, e.st, e.counters, 4, s) : launch_main(r.path, e.dd, p, r.grid, s);
     }
     if (err != hipSuccess || !reduce)
         return err;
