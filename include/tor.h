@@ -322,9 +322,9 @@ int tor_debug_zeta(tor_ctx *ctx, int nbits, const double *t, double *g_hi, doubl
  * second stream: beside a chunked launch on the 16 CUs it leaves out, or on
  * the whole device when none runs, so they wait for no chunk that those CUs
  * would outlast (a chunk takes them only while an express launch is busy or
- * one of them is more than the 16 CUs do until the chunk is due to end).  max_queue bounds the
- * requests held (admitted or waiting); tor_submit beyond it returns
- * TOR_E_BUSY.  Applies from the scheduler's next round on.  Errors:
+ * one of them is more than the 16 CUs do until the chunk is due to end).
+ * max_queue bounds the requests held (admitted or waiting); tor_submit beyond
+ * it returns TOR_E_BUSY.  Applies from the scheduler's next round on.  Errors:
  * TOR_E_INVAL (chunk_subsets < 1024, express_subsets < 0, oldest_share
  * outside [0, 1], max_queue < 1). */
 int tor_serve_config(tor_ctx *ctx, long long chunk_subsets, long long express_subsets,

@@ -35,7 +35,7 @@
 //    subsets per lane.
 // Terms are summed per lane in double-double, reduced over the wave, and
 // written to the root's partial slot; a second kernel sums the slots of each
-// matrix in index order.
+// matrix in a fixed order (the last wave of a lone evaluation of few roots does).
 // The double-double factor's instantiation of the main kernel is built in
 // tor_kernels_quad.hip, and the one-launch form of the smallest evaluations in
 // tor_small.hip; both include this file with TOR_KERNELS_TEMPLATES_ONLY defined
@@ -703,7 +703,7 @@ __device__ __forceinline__ void tierB_level(const TierB<S> &tb, RT<S> leafDet, i
     // real path: an empty asm hides that the lane index is the same in every
     // leaf, so the node and block indices of the passes of levels 3 and 4 are
     // recomputed per leaf instead of being held in registers across the whole
-    // leaf loop (levels 1 and 2 fit: 255 registers; with the others the
+    // leaf loop (levels 1 and 2 fit: 254 registers; with the others the
     // kernel passes 256 and half the waves go).  The 16-byte paths have
     // registers to spare.
     int ln = lane;
@@ -1027,9 +1027,9 @@ __device__ inline void red_step(double &h, double &l, double &ab, double &bad, i
 // (its slot is written): the wave that ends last sums the slots, in
 // the order of the reduction kernel (whose threads and waves beyond them add
 // zeros), and announces the result, instead of a launch for that alone: 17
-// modes 34.2 us a call against 37.8, 13 Hermitian ones 29.5 against 31.9.  More roots than lanes keep the
-// kernel of their own: they would all meet at this one counter (13 ns each),
-// and one wave would add several slots a lane.
+// modes 34.2 us a call against 37.8, 13 Hermitian ones 29.5 against 31.9.
+// More roots than lanes keep the kernel of their own: they would all meet at
+// this one counter (13 ns each), and one wave would add several slots a lane.
 template <bool DD>
 __device__ __forceinline__ void finish_root(const __attribute__((address_space(4))) MainParams *prm, const double *slots, int lane)
 {
@@ -1202,7 +1202,7 @@ __device__ __forceinline__ void main_wave(const MainParams &prm)
             // is the same in every leaf, so what the tiers derive from it
             // (block and node indices, table entries) is recomputed in each
             // leaf instead of being held in registers across the whole loop.
-            // That brings the kernel to 256 registers, two waves per SIMD
+            // That brings the kernel to 252 registers, two waves per SIMD
             // (the real FP64 kernel does the same for tier B only).
             int lane = threadIdx.x;
             if constexpr (std::is_same<S, ddr>::value)

@@ -2,16 +2,18 @@
 //
 // One evaluation:
 //   1. the host checks the arguments (sizes, pointers, leading dimensions);
-//   2. a host input is copied to the device as it is (a device input is read
-//      in place); the staging kernel (tor_stage.hip) validates every value,
-//      forms I - O from its lower triangle, tests the Gaussian-state
-//      structure and packs the matrix in the layout of its path, straight
-//      into the workspace; the host reads back only the path and status;
+//   2. a host input's lower triangle is packed into pinned memory, from where
+//      the staging kernel (tor_stage.hip) reads it across the bus (a device
+//      input is read in place); that kernel validates every value, forms
+//      I - O, tests the Gaussian-state structure and packs the matrix in the
+//      layout of its path, straight into the workspace;
 //   3. one persistent launch over all (matrix, subtree root) items, then the
-//      fixed-order per-matrix reduction of the root slots, one copy back.
+//      fixed-order per-matrix reduction of the root slots into pinned memory.
 //      Positive definiteness is the kernel's own test: it checks the pivots
 //      of every subset, I - O itself among them, and a failed pivot is
 //      reported as TOR_E_NOT_PD.
+// A lone evaluation (eval_one) and click_all are enqueued to their end at once,
+// their kernels acting on the verdict in device memory; a batch waits for it.
 //
 // Serving (tor_submit / tor_poll) keeps each admitted request's matrix and
 // root slots in a device pool and runs them in chunked launches: every launch
