@@ -18,8 +18,9 @@ ARCH = os.environ.get("TOR_OFFLOAD_ARCH", "gfx950")
 SOURCES = ["tor_kernels.hip", "tor_compare.hip", "tor_stage.hip", "tor_small.hip", "tor_zeta.hip", "tor_probe.hip",
            "tor_runtime.cpp"]
 # the double-double factor's kernel: its own translation unit, compiled with
-# the AMDGPU scheduler's register-pressure trackers, which schedule it about
-# 4 % faster (the FP64 kernels gain nothing from them)
+# the AMDGPU scheduler's register-pressure trackers, which scheduled it about
+# 4 % faster with seven waves per CU and cost nothing with eight (the FP64
+# kernels gain nothing from them)
 QUAD_SOURCE = "tor_kernels_quad.hip"
 QUAD_FLAGS = ["-mllvm", "-amdgpu-use-amdgpu-trackers"]
 OBJ_DIR = os.path.join(HERE, "_build")

@@ -7,9 +7,9 @@
 // that file's launchers and plain kernels, so that this unit can be compiled
 // with its own code-generation options: the library builds it with the
 // AMDGPU scheduler's register-pressure trackers (-mllvm
-// -amdgpu-use-amdgpu-trackers), which schedule this kernel about 4 % faster
-// (n = 30: 22.6 against 23.6 ms, the same results bit for bit) but the FP64
-// kernels no faster.
+// -amdgpu-use-amdgpu-trackers), which scheduled this kernel about 4 % faster
+// with seven waves per CU (n = 30: 22.6 against 23.6 ms, the same results bit
+// for bit; with eight both take 21.0 ms) but the FP64 kernels no faster.
 #define TOR_KERNELS_TEMPLATES_ONLY
 #include "tor_kernels.hip"
 

@@ -243,6 +243,30 @@ int choose_k(const tor_ctx *ctx, int N, int path)
     return std::min(LA, LA <= g + 3 ? one : LA <= g + 6 ? g + 1 : g + 3);
 }
 
+// Where the scratch is given (a caller's workspace, the static array) and too
+// small for what is fastest: no more waves than SPARE_FIT per CU on the 16-byte
+// paths, then the deeper splits of spare_k and spare_ks, whose per-wave stacks
+// are smaller.
+constexpr int SPARE_FIT = 7;
+int spare_grid(const tor_ctx *ctx, int path, int grid)
+{
+    return path == PATH_REAL ? grid : std::min(grid, ctx->num_cu * SPARE_FIT);
+}
+bool given_k(const tor_ctx *ctx, int N, int path)
+{
+    return ctx->opt.split_k > 0 || ctx->tune[path][std::min(N, MAX_N)].valid;
+}
+int spare_k(const tor_ctx *ctx, int N, int path)
+{
+    const int LA = N - path_R(path);
+    if (LA <= 0 || given_k(ctx, N, path) || path == PATH_REAL)
+        return choose_k(ctx, N, path);
+    int g = 1;
+    while ((1 << g) < spare_grid(ctx, path, default_grid(ctx, path)))
+        ++g;
+    return std::min(LA, std::max(g - 1, std::min(g + 3, LA - 5)));
+}
+
 int ensure_ws(tor_ctx *ctx, size_t bytes)
 {
     if (bytes <= ctx->ws_bytes)
@@ -844,15 +868,50 @@ int rerun_failed(tor_ctx *ctx, int path, const std::vector<ProblemDesc> &descs, 
     return TOR_OK;
 }
 
+// Workspace bytes up to which run_recursive's launch reaches.
+size_t recursive_bytes(int path, const std::vector<Mat *> &mats, const std::vector<int> &ks, size_t base, int grid)
+{
+    long long nslots = 0, stack = 0;
+    for (size_t i = 0; i < mats.size(); i++) {
+        nslots += 1ll << ks[i];
+        stack = std::max(stack, wave_stack_bytes(path, mats[i]->N, ks[i]));
+    }
+    const int count = (int)mats.size();
+    return align_up(base + sizeof(double) * 4 * (size_t)nslots, 256) + launch_layout(count, count, stack).total(grid);
+}
+
+// batch_ks where the scratch is scarce: about eight roots per wave
+void spare_ks(const tor_ctx *ctx, int path, const std::vector<Mat *> &grp, std::vector<int> &ks, int grid)
+{
+    double work = 0.0;
+    for (const Mat *m : grp)
+        work += std::ldexp(1.0, m->N);
+    const int lg = (int)std::floor(std::log2(std::max(work / (8.0 * grid), 1.0)) + 0.5);
+    for (size_t j = 0; j < grp.size(); j++) {
+        const int N = grp[j]->N;
+        ks[j] = grp.size() == 1 || ctx->opt.split_k > 0 ? spare_k(ctx, N, path)
+                                                        : std::max(0, std::min(N - lg, N - path_R(path)));
+    }
+}
+
 // Synchronous path: all roots of every staged matrix in one launch, matrices
 // with more modes first; their root slots and the launch's own data go into
 // the workspace from byte base on.  results: 4 doubles per matrix (input
 // order).
 int run_recursive(tor_ctx *ctx, int path, std::vector<Mat *> &mats, std::vector<int> &ks,
                   std::vector<double> &results, float *ms, std::vector<double> *slots_out, size_t base,
-                  std::vector<int> *launches)
+                  std::vector<int> *launches, bool own_depths = false)
 {
     const int count = (int)mats.size();
+    int Nmax = 0;
+    for (const Mat *m : mats)
+        Nmax = std::max(Nmax, m->N);
+    int grid = launch_grid(ctx, path, Nmax);
+    if (!ctx->own_ws && recursive_bytes(path, mats, ks, base, grid) > ctx->ws_bytes) {
+        grid = spare_grid(ctx, path, grid);
+        if (own_depths && recursive_bytes(path, mats, ks, base, grid) > ctx->ws_bytes)
+            spare_ks(ctx, path, mats, ks, grid);
+    }
     std::vector<int> order(count);
     for (int i = 0; i < count; i++)
         order[i] = i;
@@ -860,15 +919,12 @@ int run_recursive(tor_ctx *ctx, int path, std::vector<Mat *> &mats, std::vector<
     // workspace: slots, then what run_launch needs
     std::vector<size_t> s_off(count);
     long long nslots = 0, stack = 0;
-    int Nmax = 0;
     for (int s = 0; s < count; s++) {
         s_off[s] = base + sizeof(double) * 4 * (size_t)nslots;
         nslots += 1ll << ks[order[s]];
-        Nmax = std::max(Nmax, mats[order[s]]->N);
         stack = std::max(stack, wave_stack_bytes(path, mats[order[s]]->N, ks[order[s]]));
     }
     const size_t off = align_up(base + sizeof(double) * 4 * (size_t)nslots, 256);
-    const int grid = launch_grid(ctx, path, Nmax);
     // size the workspace for everything, keeping the staged matrices below base
     int rc = ensure_ws_keep(ctx, off + launch_layout(count, count, stack).total(grid), base);
     if (rc != TOR_OK)
@@ -1028,7 +1084,7 @@ int run_staged(tor_ctx *ctx, std::vector<Mat *> &mats, const std::vector<int> &i
         std::vector<double> res;
         std::vector<int> runs;
         float ms = 0.f;
-        int rc = run_recursive(ctx, path, grp, ks, res, &ms, slots_out, base, &runs);
+        int rc = run_recursive(ctx, path, grp, ks, res, &ms, slots_out, base, &runs, fixed_k < 0);
         if (rc != TOR_OK)
             return rc;
         for (size_t j = 0; j < grp.size(); j++) {
@@ -1942,14 +1998,23 @@ int eval_static(tor_ctx *ctx, char *base, int n, const double *O, long ld, tor_r
     m.N = info.N;
     m.path = info.path;
     const int path = info.path, N = info.N;
-    const int k = choose_k(ctx, N, path);
+    int k = choose_k(ctx, N, path), waves = launch_grid(ctx, path, N);
+    auto fits = [&]() {
+        return at + align_up(sizeof(double) * 4 * ((size_t)1 << k), 256) +
+                   (size_t)wave_stack_bytes(path, N, k) * (size_t)std::min<long long>(waves, 1ll << k) <=
+               TOR_STATIC_SCRATCH_BYTES;
+    };
+    if (!fits())
+        waves = spare_grid(ctx, path, waves);
+    if (!fits())
+        k = spare_k(ctx, N, path);
+    if (!fits())
+        return TOR_E_SCRATCH;
     const long long nroots = 1ll << k;
     double *dSlots = (double *)(base + at);
     at += align_up(sizeof(double) * 4 * (size_t)nroots, 256);
     const long long stride = wave_stack_bytes(path, N, k);
-    const int grid = (int)std::min<long long>(launch_grid(ctx, path, N), nroots);
-    if (at + (size_t)stride * grid > TOR_STATIC_SCRATCH_BYTES)
-        return TOR_E_SCRATCH;
+    const int grid = (int)std::min<long long>(waves, nroots);
     ProblemDesc pd{};
     pd.C = dForm;
     pd.slots = dSlots;
