@@ -268,6 +268,17 @@ __device__ __forceinline__ unsigned long long bcast_first(unsigned long long v)
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// The next ticket of a launch's queue, for the whole wave (every lane active):
+// one lane adds 1, so tickets are distinct however the compiler or the device
+// handles an atomic of many lanes.
+__device__ __forceinline__ unsigned long long take_ticket(unsigned long long *counter, int lane)
+{
+    unsigned long long t = 0;
+    if (lane == 0)
+        t = __hip_atomic_fetch_add(counter, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return bcast_first(t);
+}
+
 // ---- 2x2 pivot of one include step
 template <class S>
 struct Piv {

@@ -1116,14 +1116,9 @@ __device__ __forceinline__ void main_wave(const MainParams &prm)
     // part of the device, beside others): there the first items come from the
     // counter too, for an item that waits for its block ends the launch late
     // (a saturated stream of requests 1130 -> 1020 per second).
-    // Every lane adds 1 with nothing lane-dependent in the source, which the
-    // compiler turns into one atomic of 64 (adding 1 from lane 0 only became
-    // a 64-step loop over the lanes, 2 us), so a ticket is a 64th of the old
-    // value.
     const long long nfirst = prm.tickets_only ? 0 : (long long)gridDim.x;
     auto ticket = [&]() -> long long {
-        return nfirst < prm.total_items ? nfirst + (long long)(bcast_first(atomicAdd(prm.counter, 1ull)) >> 6)
-                                        : prm.total_items;
+        return nfirst < prm.total_items ? nfirst + (long long)take_ticket(prm.counter, lane) : prm.total_items;
     };
     // the descriptors are read where they lie, by scalar loads: prm.one in the
     // kernel's arguments (prm is the first of them) unless there is a list
