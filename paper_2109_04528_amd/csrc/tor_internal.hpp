@@ -250,6 +250,7 @@ struct EvalOne {
     long long *clock;  // device: when the recursive kernel started
     EvalResult *result;       // pinned
     unsigned long long done;  // its number (not 0)
+    long long fail_root;      // debug: this root reports a numeric failure (-1: none)
 };
 // null in a host-only build of the runtime without the kernels, which then
 // takes the general path

@@ -1482,6 +1482,7 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
         p.counter = e.counters + i;
         p.scratch = r.scratch;
         p.scratch_stride = r.stride;
+        p.fail_item1 = e.fail_root + 1;
         p.gate = e.st.info;
         p.gate_path = r.path;
         if (red[i] < 0) {

@@ -831,10 +831,12 @@ int rerun_failed(tor_ctx *ctx, int path, const std::vector<ProblemDesc> &descs, 
             redo.push_back((int)s);
     if (redo.empty())
         return TOR_OK;
+    // on the stream: a lone evaluation's chain may not have ended yet
     std::vector<double> hs(4 * (size_t)nslots);
-    hipError_t e = hipMemcpy(hs.data(), ctx->ws + s_off[0], sizeof(double) * 4 * nslots, hipMemcpyDeviceToHost);
-    if (e != hipSuccess)
-        return hip_status(e);
+    hipError_t e = hipMemcpyAsync(hs.data(), ctx->ws + s_off[0], sizeof(double) * 4 * nslots, hipMemcpyDeviceToHost, ctx->stream);
+    const hipError_t e2 = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess || e2 != hipSuccess)
+        return hip_status(e != hipSuccess ? e : e2);
     std::vector<ProblemDesc> rd;
     std::vector<int> rred;
     long long item1 = 0, items = 0;
@@ -847,6 +849,8 @@ int rerun_failed(tor_ctx *ctx, int path, const std::vector<ProblemDesc> &descs, 
                     lo = r;
                 hi = r;
             }
+        if (lo < 0)  // the matrix's flag without a root's
+            return TOR_E_DEVICE;
         ProblemDesc d = descs[s];
         d.root_begin = lo;
         d.nroots = hi - lo + 1;
@@ -1114,14 +1118,14 @@ constexpr std::chrono::microseconds EVAL_SPIN(300);
 // triangle is packed into pinned memory, from where the staging kernel reads
 // it; the verdict and the result are written to pinned memory by the kernels.
 // *taken is false (and nothing has been done) where the general path has to
-// run: a forced root failure, a caller's workspace that does not fit every
-// path at once, a host matrix too large to be staged through LDS.
+// run: a caller's workspace that does not fit every path at once, a host matrix
+// too large to be staged through LDS.
 int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, bool *taken)
 {
     *taken = false;
     const unsigned flags = ctx->opt.flags;
     const bool dev_in = (flags & TOR_INPUT_DEVICE) != 0;
-    if (!launch_eval_one || ctx->dbg_runs > 0 || n == 0 || (!dev_in && n > STAGE_LDS_MODES))
+    if (!launch_eval_one || n == 0 || (!dev_in && n > STAGE_LDS_MODES))
         return TOR_OK;
     const unsigned sfl = stage_flags(flags);
     const int n2 = 2 * n;
@@ -1195,6 +1199,7 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
     ev.st.info = (StageInfo *)ctx->ws;
     ev.st.out = ctx->ws + oForm;
     EvalResult *res = (EvalResult *)ctx->hdown;
+    ev.fail_root = ctx->dbg_runs > 0 ? ctx->dbg_root : -1;
     ev.stage = true;
     // The kernels of the path that is not taken follow the result of the one
     // that is.  They look at the verdict, so in a caller's workspace (which may
@@ -1266,13 +1271,16 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
         at = 0;
     }
     const EvalOne::Run &r = ev.run[at];
+    // debug: used up by this evaluation; a root beyond its split is ignored
+    const int dbg_runs = ev.fail_root >= 0 && ev.fail_root < r.P.nroots ? ctx->dbg_runs - 1 : 0;
+    ctx->dbg_runs = 0;
     const float ms = (float)res->ms;
     std::vector<int> runs(1, 1);
     double v[4] = {res->v[0], res->v[1], res->v[2], res->v[3]};
     if (v[3] == SLOT_NUMERIC) {
         std::vector<double> rv(v, v + 4);
         rc = rerun_failed(ctx, m.path, std::vector<ProblemDesc>(1, r.P), rv, std::vector<size_t>(1, oSlots), r.P.nroots, off,
-                          launch_grid(ctx, m.path, m.N), -1, -1, 0, runs);
+                          launch_grid(ctx, m.path, m.N), 0, ev.fail_root, dbg_runs, runs);
         if (rc != TOR_OK)
             return rc;
         std::copy(rv.begin(), rv.end(), v);
