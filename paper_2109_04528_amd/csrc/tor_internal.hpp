@@ -80,7 +80,8 @@ struct MainParams {
                                   // (bit N-1-l = decision at level l); else null
     const StageInfo *gate;        // run only if the staging kernel gave gate_path (null: always)
     EvalResult *result;           // a launch of one matrix with few roots: its sum goes here (or null)
-    unsigned long long *finished; // with result: roots that are done, zero before the launch
+    unsigned long long *finished; // with result: roots that are done (blocks that the gate keeps from
+                                  // running: that have looked), zero before the launch
     unsigned long long done;      // with result: the number to announce (or 0)
     int done_gated;               // the last launch of its chain: it announces also where the gate
     int quiet_path;               // keeps it from running, but for this path's own kernel having done so

@@ -1096,8 +1096,12 @@ __device__ __forceinline__ void main_wave(const MainParams &prm)
 
     const int lane = threadIdx.x;
     if (prm.gate && prm.gate->path != prm.gate_path) {
-        // the matrix has another path, or is not valid
-        if (prm.done_gated && prm.gate->path != prm.quiet_path && blockIdx.x == 0 && lane == 0)
+        // the matrix has another path, or is not valid.  The block that looks
+        // last announces it: behind the end nothing may touch the workspace,
+        // which may be the caller's (their looks come first in each block, and
+        // a count of one address for up to RESULT_ROOTS blocks)
+        if (prm.done_gated && prm.gate->path != prm.quiet_path && lane == 0 &&
+            __hip_atomic_fetch_add(prm.finished, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x)
             announce(prm.result, prm.gate, prm.done);
         return;
     }
@@ -1469,7 +1473,8 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
     // the paths whose roots a kernel of their own has to sum
     int red[2] = {-2, -2}, quiet = -2;
     for (int i = 0; i < e.nrun; ++i)
-        if (e.run[i].P.nroots > RESULT_ROOTS)
+        // (fewer waves than roots would still look for tickets behind the end)
+        if (e.run[i].P.nroots > RESULT_ROOTS || e.run[i].grid < e.run[i].P.nroots)
             red[i] = e.run[i].path;
     const bool reduce = red[0] >= 0 || red[1] >= 0;
     for (int i = 0; i < e.nrun && err == hipSuccess; ++i) {
