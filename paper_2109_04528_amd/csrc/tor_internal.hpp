@@ -84,7 +84,7 @@ struct MainParams {
                                   // running: that have looked), zero before the launch
     unsigned long long done;      // with result: the number to announce (or 0)
     int done_gated;               // the last launch of its chain: it announces also where the gate
-    int quiet_path;               // keeps it from running, but for this path's own kernel having done so
+                                  // keeps it from running
     long long *clock;             // the device clock at the kernel's start goes here (or null)
     double ms_per_tick;           // of that clock
     int tickets_only;             // blocks may start late: no item is any block's own
@@ -236,7 +236,6 @@ constexpr int FMA_PROBE_CHAINS = 16;
 // matrix is staged already (st.info holds the verdict).
 struct EvalOne {
     bool stage;
-    bool early;                    // an unused path's kernels may end after the result is there
     StageDesc st;                  // st.info: device memory
     unsigned long long *counters;  // device: 2 queue heads, 2 counts of finished roots
     int nrun;

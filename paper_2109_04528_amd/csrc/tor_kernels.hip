@@ -1026,8 +1026,8 @@ __device__ inline void red_step(double &h, double &l, double &ab, double &bad, i
 // The end of a root of a lone evaluation with at most RESULT_ROOTS of them
 // (its slot is written): the wave that ends last sums the slots, in
 // the order of the reduction kernel (whose threads and waves beyond them add
-// zeros), and announces the result, instead of a launch for that alone: 17
-// modes 34.2 us a call against 37.8, 13 Hermitian ones 29.5 against 31.9.
+// zeros), and announces the result if it is the last launch of its chain, instead
+// of a launch for that alone: 13 Hermitian modes 29.5 us a call against 31.9.
 // More roots than lanes keep the kernel of their own: they would all meet at
 // this one counter (13 ns each), and one wave would add several slots a lane
 // (256 roots, real n = 19: 37.0 us a call against 35.3; 128, n = 18: 33.3
@@ -1100,7 +1100,7 @@ __device__ __forceinline__ void main_wave(const MainParams &prm)
         // last announces it: behind the end nothing may touch the workspace,
         // which may be the caller's (their looks come first in each block, and
         // a count of one address for up to RESULT_ROOTS blocks)
-        if (prm.done_gated && prm.gate->path != prm.quiet_path && lane == 0 &&
+        if (prm.done_gated && lane == 0 &&
             __hip_atomic_fetch_add(prm.finished, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x)
             announce(prm.result, prm.gate, prm.done);
         return;
@@ -1372,12 +1372,11 @@ __global__ void __launch_bounds__(RED_THREADS) tor_reduce(const ProblemDesc *pro
 }
 
 // one matrix, of the path the staging kernel gave it (a or b); the end of its
-// chain (quiet_path: that path's own kernel has announced the result)
+// chain
 template <bool DD>
 __global__ void __launch_bounds__(RED_THREADS) tor_reduce_one(const StageInfo *gate, int path_a, ProblemDesc a, int path_b,
-                                                              ProblemDesc b, int quiet_path, const long long *clock,
-                                                              double ms_per_tick, EvalResult *result,
-                                                              unsigned long long done)
+                                                              ProblemDesc b, const long long *clock, double ms_per_tick,
+                                                              EvalResult *result, unsigned long long done)
 {
     __shared__ double r[4];
     const int path = gate->path;
@@ -1395,8 +1394,7 @@ __global__ void __launch_bounds__(RED_THREADS) tor_reduce_one(const StageInfo *g
                 st_host(&result->v[j], r[j]);
             st_host(&result->ms, ms);
         }
-        if (path != quiet_path)
-            announce(result, gate, done);
+        announce(result, gate, done);
     }
 }
 
@@ -1471,7 +1469,7 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
                      : e.stage ? launch_stage_one(e.st, e.counters, 4, s)
                                : launch_zero(e.counters, 4, s);
     // the paths whose roots a kernel of their own has to sum
-    int red[2] = {-2, -2}, quiet = -2;
+    int red[2] = {-2, -2};
     for (int i = 0; i < e.nrun; ++i)
         // (fewer waves than roots would still look for tickets behind the end)
         if (e.run[i].P.nroots > RESULT_ROOTS || e.run[i].grid < e.run[i].P.nroots)
@@ -1491,16 +1489,11 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
         p.gate = e.st.info;
         p.gate_path = r.path;
         if (red[i] < 0) {
-            // the result is announced as soon as it is there, or by the
-            // chain's last kernel
             p.result = e.result;
             p.finished = e.counters + 2 + i;
-            p.done = e.early || last ? e.done : 0;
-            if (e.early && !last)
-                quiet = r.path;
+            p.done = last ? e.done : 0;
         }
         p.done_gated = last;
-        p.quiet_path = quiet;
         p.clock = e.clock;
         p.ms_per_tick = wall_ms_per_tick();
         err = small && i == 0 ? launch_small(r.path, p, e.st, e.counters, 4, s) : launch_main(r.path, e.dd, p, r.grid, s);
@@ -1509,10 +1502,10 @@ hipError_t launch_eval_one(const EvalOne &e, hipStream_t s)
         return err;
     const ProblemDesc &a = e.run[0].P, &b = e.run[e.nrun - 1].P;
     if (e.dd)
-        hipLaunchKernelGGL((tor_reduce_one<true>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, red[0], a, red[1], b, quiet, e.clock,
+        hipLaunchKernelGGL((tor_reduce_one<true>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, red[0], a, red[1], b, e.clock,
                            wall_ms_per_tick(), e.result, e.done);
     else
-        hipLaunchKernelGGL((tor_reduce_one<false>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, red[0], a, red[1], b, quiet, e.clock,
+        hipLaunchKernelGGL((tor_reduce_one<false>), dim3(1), dim3(RED_THREADS), 0, s, e.st.info, red[0], a, red[1], b, e.clock,
                            wall_ms_per_tick(), e.result, e.done);
     return hipGetLastError();
 }

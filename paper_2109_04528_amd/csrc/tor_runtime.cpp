@@ -1201,10 +1201,6 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
     EvalResult *res = (EvalResult *)ctx->hdown;
     ev.fail_root = ctx->dbg_runs > 0 ? ctx->dbg_root : -1;
     ev.stage = true;
-    // The kernels of the path that is not taken follow the result of the one
-    // that is.  They look at the verdict, so in a caller's workspace (which may
-    // be used for anything once the call has returned) they come first.
-    ev.early = ctx->own_ws;
     ev.counters = (unsigned long long *)(ctx->ws + oCount);
     ev.nrun = np;
     ev.dd = ctx->opt.accum != TOR_ACCUM_FP64 || paths[0] == PATH_QUAD;
