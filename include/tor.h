@@ -160,7 +160,8 @@ int tor_eval(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out);
 /* For callers that cannot allocate device or pinned memory -- code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc: the
  * same evaluation as tor_eval (same kernels, same split, the same value
- * bit for bit), using only a device array the library declares statically,
+ * bit for bit; tor_eval itself splits deeper only in a caller's workspace too
+ * small for its usual split), using only a device array the library declares statically,
  * TOR_STATIC_SCRATCH_BYTES (128 MiB) per GPU, held from the first context
  * created on that GPU until the process ends.  It calls no hipMalloc,
  * hipFree, hipHostMalloc or host heap allocation, and uses neither the
@@ -168,7 +169,7 @@ int tor_eval(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out);
  * O is a host pointer (copied into the array) or, with TOR_INPUT_DEVICE,
  * device memory read in place.  The array holds the staged matrix, the
  * root slots and the per-wave stacks of one call at a time: every path fits
- * for n <= 30; beyond that the call returns TOR_E_SCRATCH when the launch's
+ * for n <= 31; beyond that the call returns TOR_E_SCRATCH when the launch's
  * stacks do not fit (the real quadrature path fits up to n = 34).  Calls on
  * one GPU share its array and keep the last call's contents; the library
  * serialises them with a per-device lock (calls that overlapped would race

@@ -231,9 +231,14 @@ int choose_k(const tor_ctx *ctx, int N, int path)
         // at 10, 83.5 at 11; n = 23 227 at 11, 244 at 12; n = 24 (LA = 15) 398 at
         // 12, 408 at 11, 471 at 13; n = 26 1413 at 12, 1483 at 11, 1579 at 13; n =
         // 30 20 947 at 12, 20 983 at 13, 23 597 at 11
+        // Beyond LA = g + 10 one more (complex) or two (double-double), so that
+        // the static array of tor_eval_static, which splits as tor_eval does,
+        // still holds the stacks of seven waves per CU: complex n = 31 16 959 at
+        // 14, 16 815 at 13; double-double n = 30 20 878 at 13, 20 893 at 12; n =
+        // 31 41 767 at 14, 41 443 at 13
         if (path == PATH_QUAD)
-            return std::min(LA, LA <= g + 1 ? g - 1 : LA <= g + 3 ? g : g + 1);
-        return std::min(LA, LA <= g + 1 ? g - 1 : LA <= g + 6 ? g : g + 2);
+            return std::min(LA, LA <= g + 1 ? g - 1 : LA <= g + 3 ? g : LA <= g + 9 ? g + 1 : LA <= g + 10 ? g + 2 : g + 3);
+        return std::min(LA, LA <= g + 1 ? g - 1 : LA <= g + 6 ? g : LA <= g + 10 ? g + 2 : g + 3);
     }
     // a grid of less than a power of two of waves: at k = g a few waves run a
     // second root alone, so k = g - 1 (measured with 1792 waves)
@@ -245,8 +250,8 @@ int choose_k(const tor_ctx *ctx, int N, int path)
 
 // Where the scratch is given (a caller's workspace, the static array) and too
 // small for what is fastest: no more waves than SPARE_FIT per CU on the 16-byte
-// paths, then the deeper splits of spare_k and spare_ks, whose per-wave stacks
-// are smaller.
+// paths, then, in a caller's workspace, the deeper splits of spare_k and
+// spare_ks, whose per-wave stacks are smaller.
 constexpr int SPARE_FIT = 7;
 int spare_grid(const tor_ctx *ctx, int path, int grid)
 {
@@ -2002,7 +2007,8 @@ int eval_static(tor_ctx *ctx, char *base, int n, const double *O, long ld, tor_r
     m.N = info.N;
     m.path = info.path;
     const int path = info.path, N = info.N;
-    int k = choose_k(ctx, N, path), waves = launch_grid(ctx, path, N);
+    const int k = choose_k(ctx, N, path);  // tor_eval's, so that the value is too
+    int waves = launch_grid(ctx, path, N);
     auto fits = [&]() {
         return at + align_up(sizeof(double) * 4 * ((size_t)1 << k), 256) +
                    (size_t)wave_stack_bytes(path, N, k) * (size_t)std::min<long long>(waves, 1ll << k) <=
@@ -2010,8 +2016,6 @@ int eval_static(tor_ctx *ctx, char *base, int n, const double *O, long ld, tor_r
     };
     if (!fits())
         waves = spare_grid(ctx, path, waves);
-    if (!fits())
-        k = spare_k(ctx, N, path);
     if (!fits())
         return TOR_E_SCRATCH;
     const long long nroots = 1ll << k;
