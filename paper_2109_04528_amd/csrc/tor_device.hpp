@@ -369,19 +369,25 @@ struct AccDD {
 //
 // Every term is positive, so each sum only grows from A; if it ends below 2A,
 // every term was below A and every addition exact.  close() tests that; if it
-// fails in any lane, the leaf runs again with AccDD, and the anchor is put
-// higher for the leaves that follow.  Nothing is assumed of the matrix.
+// fails in any lane, the leaf runs again with AccDD, and the anchors are put
+// higher for the leaves that follow; where the highest do not do, all leaves
+// that follow run with AccDD alone.
 //
-// The anchor is one for the wave, 2^lift times the first lane's first term
-// (the term of that lane's node alone, the smallest of the leaf for a Gaussian
-// state) to within a factor of 2.  The rounding errors that are summed in Pl
-// and Ml are multiples of the unit of the smallest term, at most 2^(lift - 53)
-// of it each, so sums of 16 stay exact up to lift = 50.  P - M is exact: both
-// are multiples of the unit of A and below 2A.
-// 2^lift times the power of two at det^(-1/2) of the first lane
+// The anchor is each lane's own, 2^lift times its first term (that of its node
+// alone, the smallest it adds for a Gaussian state) to within a factor of 2, so
+// that only the five modes below the node spread its terms: 2^34 holds to a
+// squeezing of r = 5.4 (one anchor for the wave, over the leaf's eleven modes,
+// held to 2.8 and made 27 modes of r = 4.4 573 us a call instead of 371, and AccDD
+// 448).  The rounding errors that are summed in Pl and Ml are multiples of the
+// unit of the smallest term, at most 2^(lift - 53) of the first one each, so sums
+// of 16 stay exact up to lift = 50 while no term is below the first, and at lift =
+// 34 down to terms of 2^-16 of it.  Beyond that they round, at 2^-102 of A (2^-68
+// of the first term), far below the rounding of that term itself.  P - M is
+// exact: both are multiples of the unit of A and below 2A.
+// 2^lift times the power of two at det^(-1/2)
 __device__ __forceinline__ double anchor_above(double det, int lift)
 {
-    const unsigned h = __builtin_amdgcn_readfirstlane((unsigned)(__builtin_bit_cast(unsigned long long, det) >> 32));
+    const unsigned h = (unsigned)(__builtin_bit_cast(unsigned long long, det) >> 32);
     const int e = (int)((h >> 20) & 0x7ffu) - 1023;
     const unsigned a = (unsigned)(1023 - (e >> 1) + lift) << 20;
     return __builtin_bit_cast(double, (unsigned long long)a << 32);
@@ -403,6 +409,7 @@ struct AccAnchor {
     static constexpr double frame = 1.0;
     __device__ __forceinline__ void begin_leaf(double *) {}
     __device__ __forceinline__ void set_frame(double) {}
+    __device__ __forceinline__ bool usable() const { return lift <= LIFT_MAX; }
     __device__ __forceinline__ double anchor(double det) const { return anchor_above(det, lift); }
     __device__ __forceinline__ void open(double a)
     {
@@ -448,8 +455,8 @@ struct AccAnchor {
         // the empty asm keeps the rounding errors with their additions: left to
         // the success branch, they hold every term and every partial sum
         __asm__ volatile("" : "+v"(Pl), "+v"(Ml));
-        if (!__all(P < 2.0 * a && M < 2.0 * a && lift <= LIFT_MAX)) {
-            lift = min(lift + 5, LIFT_MAX + 1);
+        if (!__all(P < 2.0 * a && M < 2.0 * a)) {
+            lift += 5;
             return false;
         }
         fold(s, P - M, Pl - Ml, ((P - a) + (M - a)) + (Pl + Ml));
@@ -498,6 +505,7 @@ struct AccStore {
     double P, Pl;
     double *out = nullptr;
     __device__ __forceinline__ void begin_leaf(double *p) { out = p; }
+    __device__ __forceinline__ bool usable() const { return true; }
     __device__ __forceinline__ double anchor(double det) const { return anchor_above(det, AccAnchor::LIFT0); }
     __device__ __forceinline__ void open(double a)
     {

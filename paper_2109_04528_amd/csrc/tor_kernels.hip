@@ -964,18 +964,22 @@ __device__ __forceinline__ void tierC(const TierB<S> &tb, RT<S> leafDet, int lea
                                       int &bad, bool full_leaf)
 {
     double sign, anchor;
-    tierC_terms<S, T, B, L, Acc>(tb, leafDet, leafInc, N, lane, acc, bad, full_leaf, sign, anchor);
     if constexpr (Acc::kAnchored) {
-        if (!acc.close(sign, anchor)) {
+        if (acc.usable()) {
+            tierC_terms<S, T, B, L, Acc>(tb, leafDet, leafInc, N, lane, acc, bad, full_leaf, sign, anchor);
+            if (acc.close(sign, anchor))
+                return;
             // once more from the LDS nodes, which are as they were (the empty
             // asm: nothing of the first run is kept for this one)
             __asm__ volatile("" : "+v"(lane));
-            if constexpr (Acc::kDD) {
-                AccDD leaf;
-                tierC_terms<S, T, B, L, AccDD>(tb, leafDet, leafInc, N, lane, leaf, bad, full_leaf, sign, anchor);
-                acc.fold(sign, leaf.hi, leaf.lo, leaf.abs_sum);
-            }
         }
+        if constexpr (Acc::kDD) {
+            AccDD leaf;
+            tierC_terms<S, T, B, L, AccDD>(tb, leafDet, leafInc, N, lane, leaf, bad, full_leaf, sign, anchor);
+            acc.fold(sign, leaf.hi, leaf.lo, leaf.abs_sum);
+        }
+    } else {
+        tierC_terms<S, T, B, L, Acc>(tb, leafDet, leafInc, N, lane, acc, bad, full_leaf, sign, anchor);
     }
 }
 
