@@ -585,6 +585,8 @@ struct TuckedPivots {
     using Place = NodePlacement<R, BL, (int)sizeof(S), L, 0>;
     static constexpr Place place{};
     static constexpr int AT = 16 * (Place::LIVE + NB(R - BL)), ROOM = 16 * NB(R) - AT;
+    // the pass that forms level 2 reads pivots there and node 0's first NB(R - 1) blocks
+    static_assert(Place::LIVE + NB(R - BL) >= NB(R - 1), "pivots behind the blocks that are still read");
     static_assert((int)sizeof(S) << (BL - 1) <= ROOM && (int)sizeof(RT<S>) << (BL - 1) <= ROOM, "one entry per include node");
     // array a of level J, from the start of the buffer
     static constexpr int at(int J, int a)
