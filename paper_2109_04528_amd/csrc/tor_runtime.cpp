@@ -1123,8 +1123,8 @@ constexpr std::chrono::microseconds EVAL_SPIN(300);
 // triangle is packed into pinned memory, from where the staging kernel reads
 // it; the verdict and the result are written to pinned memory by the kernels.
 // *taken is false (and nothing has been done) where the general path has to
-// run: a caller's workspace that does not fit every path at once, a host matrix
-// too large to be staged through LDS.
+// run: a workspace, or device memory for one, that does not fit every path at
+// once, a host matrix too large to be staged through LDS.
 int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, bool *taken)
 {
     *taken = false;
@@ -1185,6 +1185,10 @@ int eval_one(tor_ctx *ctx, int n, const double *O, long ld, tor_result *out, boo
     if (need > ctx->ws_bytes && !ctx->own_ws)
         return TOR_OK;
     int rc = ensure_ws(ctx, need);
+    if (rc == TOR_E_NOMEM) {  // one path alone may fit
+        (void)hipGetLastError();  // the launches that follow would report it
+        return TOR_OK;
+    }
     if (rc == TOR_OK && !dev_in)
         rc = pin_grow(ctx->hup, ctx->hup_bytes, sizeof(c64) * raw_entries(n2, sfl));
     if (rc == TOR_OK)

@@ -5,6 +5,7 @@
 //   fail    make root g_fail_root of its first run report a numeric failure;
 //   late    write the slots after it has announced the result, as a host that
 //           does not wait for the stream may find them.
+// hipMalloc (linked with --wrap) refuses allocations above g_alloc_limit.
 // Exit status 0 when every scenario passes.
 #include <hip/hip_runtime.h>
 
@@ -24,6 +25,7 @@ namespace {
 std::atomic<long long> g_fail_root{-1};
 std::atomic<bool> g_late{false};
 std::atomic<int> g_chains{0};
+std::atomic<size_t> g_alloc_limit{~(size_t)0};
 int g_failed = 0;
 
 void check(bool ok, const char *what, int i = -1)
@@ -34,6 +36,13 @@ void check(bool ok, const char *what, int i = -1)
     }
 }
 }  // namespace
+
+hipError_t real_malloc(void **p, size_t bytes) __asm__("__real__Z9hipMallocPPvm");
+hipError_t wrap_malloc(void **p, size_t bytes) __asm__("__wrap__Z9hipMallocPPvm");
+hipError_t wrap_malloc(void **p, size_t bytes)
+{
+    return bytes > g_alloc_limit ? (hipError_t)hipErrorOutOfMemory : real_malloc(p, bytes);
+}
 
 namespace tor {
 
@@ -121,6 +130,33 @@ int main()
                 check(tor_eval(ctx, n, O.data(), 2L * n, &r) == TOR_OK && r.launches == 1, "used up", n);
                 tor_destroy(ctx);
             }
+    // device memory for one path's launch but not for either's: whatever a batch
+    // of one is given, a lone evaluation is given too
+    int refused = 0, general_path = 0;
+    for (int n : {14, 22, 30})
+        for (size_t limit = (size_t)1 << 20; limit <= (size_t)400 << 20; limit += limit / 8) {
+            g_alloc_limit = limit;
+            std::vector<double> O(8 * (size_t)n * n, 0.0);
+            O[0] = 0.25;
+            O[2 * ((size_t)n * 2 * n + n)] = O[0];
+            const double *ptr = O.data();
+            const long ld = 2L * n;
+            tor_ctx *a = nullptr, *b = nullptr;
+            check(tor_create(&a, nullptr) == TOR_OK && tor_create(&b, nullptr) == TOR_OK, "create");
+            tor_result ra{}, rb{};
+            const int before = g_chains;
+            const int rca = tor_eval(a, n, ptr, ld, &ra), rcb = tor_eval_batch(b, 1, &n, &ptr, &ld, &rb);
+            check(rca == rcb || rca == TOR_OK, "served within the limit", n);
+            if (rca == TOR_OK && rcb == TOR_OK) {
+                check(ra.tor == rb.tor && ra.path == rb.path, "value within the limit", n);
+                general_path += g_chains == before;
+            } else {
+                ++refused;
+            }
+            tor_destroy(a);
+            tor_destroy(b);
+        }
+    check(refused > 0 && general_path > 0, "limits on both sides");
     std::printf("done %d\n", g_failed);
     return g_failed;
 }
