@@ -1553,8 +1553,8 @@ __global__ void tor_click_end(const long long *clock, double ms_per_tick, ClickR
 // What bounds a small call is the chain of its launches: six kernels and
 // nothing between them.  A copy each for the state, the descriptors,
 // sqrt(det) and the verdict, an event on either side of two of the kernels and
-// a wait before the transform made the 15 modes' call 111 us, against 69 so
-// (25 modes: 777 and 743).
+// a wait before the transform made the 15 modes' call 111 us, against 70 so
+// (25 modes: 777 and 745).
 hipError_t launch_click_all(const ClickAll &c, hipStream_t s)
 {
     hipError_t err = launch_stage_det(c.st, c.counter, c.det, s);

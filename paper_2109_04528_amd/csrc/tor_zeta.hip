@@ -31,8 +31,8 @@
 //   * the bits between, if any, up to 5 in registers alone (tor_zeta_bits) or
 //     6 to 8 by tiles.
 // At M = 25 that is 12 + 5 + 8 bits in three passes against 10 + 5 + 5 + 5 and
-// a permutation, 2.9 GB against 5.1 with the terms, 566 us against 980 (5.1, 5.0 and
-// 4.2 TB/s; a 1 GiB copy moves 4.8); at M = 32 12 + 4 +
+// a permutation, 2.9 GB against 5.1 with the terms, 569 us against 980 (5.0, 5.2 and
+// 4.0 TB/s; a 1 GiB copy moves 4.8); at M = 32 12 + 4 +
 // 8 + 8 in four against six passes.
 //
 // Exactness: for a Gaussian state every subset determinant is at most 1
