@@ -30,6 +30,8 @@
 //
 // A pattern (sel) stages the principal submatrix of an M-mode O on the rows
 // and columns {s, s + M : s in sel}, the matrix of a click pattern.
+#include <cfloat>
+
 #include "tor_stage.hpp"
 
 namespace tor {
@@ -50,6 +52,21 @@ __global__ void __launch_bounds__(NT) tor_stage_one(StageDesc D, unsigned long l
         zero[threadIdx.x] = 0ull;
     __shared__ c64 tri[STAGE_LDS_ENTRIES];
     stage_matrix<NT, STAGE_LDS_ENTRIES>(D, tri);
+}
+
+// A pivot whose determinant (or a square on the way to it) leaves the range of
+// a double, entry by entry: an infinite one (of an input that is rejected only
+// where a pattern holds it) divides its rows to nothing, as in a Cholesky
+// factorisation.  root: of the determinant; false if the second pivot is not
+// positive.
+__device__ __attribute__((noinline)) bool wide_pivot(double a, c64 b, double g, Piv<c64> &pv, double &root)
+{
+    pv.inv_a = isinf(a) ? 0.0 : 1.0 / a;
+    pv.ba = scale(b, pv.inv_a);
+    const double g1 = g - (b.x * pv.ba.x + b.y * pv.ba.y);
+    pv.inv_g = isinf(g1) ? 0.0 : 1.0 / g1;
+    root = sqrt(a) * sqrt(g1);
+    return g1 > 0.0;
 }
 
 // sqrt(det(I - O)) of an M-mode O (device, leading dimension ld, 0: packed
@@ -79,10 +96,15 @@ __device__ __forceinline__ void sqrt_det_lds(const double *O, long ld, int M, do
     bool bad = false;
     for (int m = M - 1; m >= 0; --m) {
         const int d = bidx(m, m);
-        const Piv<c64> pv = pivot<c64>(A[0][d].x, A[2][d], A[3][d].x);
-        if (!(A[0][d].x > 0.0) || !(pv.pdet > 0.0))
+        const double al = A[0][d].x;
+        Piv<c64> pv = pivot<c64>(al, A[2][d], A[3][d].x);
+        double root = sqrt(pv.pdet);
+        bool ok = pv.pdet > 0.0;
+        if (!isfinite(pv.pdet) || fabs(pv.pdet) < DBL_MIN)
+            ok = wide_pivot(al, A[2][d], A[3][d].x, pv, root);
+        if (!(al > 0.0) || !ok)
             bad = true;
-        prod *= sqrt(pv.pdet);
+        prod *= root;
         for (int bi = t; bi < NB(m); bi += NT) {
             int a, b;
             block_ab(bi, a, b);
