@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(NT) tor_stage_one(StageDesc D, unsigned long l
 // where a pattern holds it) divides its rows to nothing, as in a Cholesky
 // factorisation.  root: of the determinant; false if the second pivot is not
 // positive.
-__device__ __attribute__((noinline)) bool wide_pivot(double a, c64 b, double g, Piv<c64> &pv, double &root)
+__device__ __forceinline__ bool wide_pivot(double a, c64 b, double g, Piv<c64> &pv, double &root)
 {
     pv.inv_a = isinf(a) ? 0.0 : 1.0 / a;
     pv.ba = scale(b, pv.inv_a);
@@ -100,7 +100,8 @@ __device__ __forceinline__ void sqrt_det_lds(const double *O, long ld, int M, do
         Piv<c64> pv = pivot<c64>(al, A[2][d], A[3][d].x);
         double root = sqrt(pv.pdet);
         bool ok = pv.pdet > 0.0;
-        if (!isfinite(pv.pdet) || fabs(pv.pdet) < DBL_MIN)
+        // the same in every lane: a scalar branch
+        if (__builtin_amdgcn_readfirstlane(!isfinite(pv.pdet) || fabs(pv.pdet) < DBL_MIN))
             ok = wide_pivot(al, A[2][d], A[3][d].x, pv, root);
         if (!(al > 0.0) || !ok)
             bad = true;
